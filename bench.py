@@ -25,21 +25,24 @@ sys.path.insert(0, ROOT)
 
 import workloads  # noqa: E402  (seeded plaintext inputs only)
 
-# Algorithmic work of one gate bootstrap, in 32-bit integer lane operations,
-# for the radix-2 NTT form of the method: 500 CMux x (6 NTT-1024 of 5,120
-# butterflies + 8 x 1,024 pointwise products + their sums).
-#   arith 0 (NTT over p = 2^64 - 2^32 + 1): 26 lane-ops per modmul (four
-#     32x32->64 products and the reduction), 4 per modular add/sub.
-#   arith 1 (NTT modulo two 28-bit primes): per prime, 3 per Montgomery
-#     modmul and 1 per add/sub; plus the CRT recombination of the 2 x 1,024
-#     output coefficients (7 each).
+# Algorithmic work of one gate bootstrap, in lane operations of the
+# vector ALU.
+#   arith 0 (NTT over p = 2^64 - 2^32 + 1): 32-bit integer operations of the
+#     radix-2 form, 500 CMux x (6 NTT-1024 of 5,120 butterflies + 8 x 1,024
+#     pointwise products + their sums): 26 per modmul (four 32x32->64 products
+#     and the reduction), 4 per modular add/sub.
+#   arith 1 (double-precision FFT, key in two halves): f64 fused multiply-adds,
+#     500 CMux x (8 FFTs of 512 complex points, 9 x 256 butterflies of six,
+#     + 16 x 512 complex multiply-adds of four + the twist of 4 x 512 outputs,
+#     four each).
 MODMUL_PER_CMUX = 6 * 5120 + 8 * 1024
 MODADD_PER_CMUX = 6 * 5120 * 2 + 8 * 1024
 LANE_OPS_PER_GATE = {
     0: 500 * (26 * MODMUL_PER_CMUX + 4 * MODADD_PER_CMUX),
-    1: 500 * (2 * (3 * MODMUL_PER_CMUX + MODADD_PER_CMUX) + 7 * 2 * 1024),
+    1: 500 * (8 * 9 * 256 * 6 + 16 * 512 * 4 + 4 * 512 * 4),
 }
-# 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one 32-bit integer op per lane-cycle.
+# 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one 32-bit integer op or one f64
+# fused multiply-add (78.6 TFLOP/s) per lane-cycle.
 VALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 # Key switching gathers rows of the key-switching key: per gate 1,024 input
 # coefficients x 8 base-4 digits, three quarters of them non-zero on average,
@@ -51,7 +54,7 @@ KS_BYTES_PER_GATE = 1024 * 8 * 3 // 4 * 501 * 4
 L2_PEAK_TBS = 8 * 16 * 128 * 2.4e9 / 1e12
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "blind_rotate_traffic.json")
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2005_01945_amd", "csrc", f)
-               for f in ("kernels.hip", "goldilocks.h", "modq.h")]
+               for f in ("kernels.hip", "fft.h", "goldilocks.h")]
 
 
 def log(msg):
@@ -322,7 +325,10 @@ def roofline_of(records):
     gates_per_launch = dom["gates"] / dom["launches"]
     avg_launch_ms = dom["ms"] / dom["launches"]
     achieved = LANE_OPS_PER_GATE[shape[2]] * gates_per_launch / (avg_launch_ms / 1e3) / 1e12
-    kernel = f"k_blind_rotate_pair<{shape[2]}>" if shape[0] == 2 else f"k_blind_rotate<{shape[1]}, {shape[2]}>"
+    if shape[2] == 1:
+        kernel = "k_blind_rotate_group" if shape[0] == 1 else f"k_blind_rotate_fft<{shape[0]}>"
+    else:
+        kernel = "k_blind_rotate_pair" if shape[0] == 2 else f"k_blind_rotate<{shape[1]}>"
     roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": round(VALU_PEAK_TOPS, 2),
                 "unit": "TOP/s", "frac": round(achieved / VALU_PEAK_TOPS, 4),
                 "traffic": measured_traffic(kernel, gates_per_launch),
@@ -705,7 +711,7 @@ def main():
         log(f"CPU parallel framework: {cpu_par}")
 
     shape = res.pop("_shape")
-    dtype = ("u32 (Torus32) / i32 residues mod two 28-bit primes (NTT)" if shape[2] == 1
+    dtype = ("u32 (Torus32) / f64 (FFT products, exactly rounded)" if shape[2] == 1
              else "u32 (Torus32) / u64 (NTT mod 2^64-2^32+1)")
     line = {
         "metric": "bootstrapped gates/sec on 1 MI355X (batched vs plain) + p50/p99 latency per 32-bit mul",

@@ -160,9 +160,9 @@ int fhe_phase(const fhe_secret_key* sk, const uint32_t* ct, size_t count, int32_
 /* ---------------------------------------------------------------------- */
 
 /* Uploads the cloud key to HIP device `device`, converts the bootstrapping
- * key to the NTT domains of both arithmetics (modulo two 28-bit primes, the
- * default, and over p = 2^64 - 2^32 + 1; 32.8 MB each) and lays out the
- * key-switching key for row gathers (50.3 MB).  The cloud key may be freed
+ * key for both arithmetics (the FFT domain, the default, in two layouts of
+ * 65.5 MB, and the NTT domain over p = 2^64 - 2^32 + 1, 32.8 MB) and lays out
+ * the key-switching key for row gathers (50.3 MB).  The cloud key may be freed
  * afterwards.  Errors: FHE_EDEVICE if the device is missing or not gfx950;
  * FHE_ENOMEM if device memory runs out. */
 int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out);
@@ -177,7 +177,7 @@ void fhe_ctx_destroy(fhe_ctx* ctx);
  * vector, sample extraction and key switching, all gates of the batch in one
  * launch per step.  ops: device uint8[count]; in0, in1, out: device
  * uint32[count][n+1].  count = 0 is a no-op.  The result is bit-exact with
- * the definition (exact NTT arithmetic).  The codes live in device memory: a
+ * the definition (exact arithmetic).  The codes live in device memory: a
  * code outside FHE_AND..FHE_ORYN (including the three-input codes, which need
  * fhe_bootstrap_gate3_batch) gives the all-zero output sample and is reported
  * as FHE_EINVAL by the context's next batched call or fhe_ctx_check. */
@@ -355,12 +355,14 @@ int fhe_ctx_set_graphs(fhe_ctx* ctx, int enable);
 /* (bucket b covers widths 2^(b-1) < w <= 2^b, the last bucket, b = 15,     */
 /* every width above 2^14).  Shapes:                                        */
 /*   waves_per_gate = 1, gates_per_group in {1, 2, 4, 8}: one wavefront per */
-/*     gate, that many ciphertexts per workgroup (throughput shape);        */
+/*     gate (throughput shape); arith 0: that many ciphertexts per          */
+/*     workgroup; arith 1: always groups of four ciphertexts that share     */
+/*     their key loads;                                                     */
 /*   waves_per_gate = 2, gates_per_group = 1: two wavefronts split every    */
 /*     CMux of one gate (latency shape for levels narrower than the chip);  */
-/*   each of these with either NTT arithmetic (arith 0 or 1);               */
+/*   each of these with either arithmetic (arith 0 or 1);                   */
 /*   waves_per_gate = 4, gates_per_group = 1, arith = 1: four wavefronts    */
-/*     per gate, one per (polynomial, prime) (lowest latency).              */
+/*     per gate, one per digit row (lowest latency).                        */
 /* The shape changes only the schedule and the exact arithmetic used to     */
 /* reach the result: every shape computes the same words.  Captured level   */
 /* schedules are recaptured after a change.                                 */
@@ -368,8 +370,9 @@ int fhe_ctx_set_graphs(fhe_ctx* ctx, int enable);
 typedef struct {
     uint32_t waves_per_gate;
     uint32_t gates_per_group;
-    uint32_t arith;  /* 0: NTT over p = 2^64 - 2^32 + 1; 1: NTT modulo two
-                        28-bit primes, recombined by CRT (both exact) */
+    uint32_t arith;  /* 0: NTT over p = 2^64 - 2^32 + 1; 1: FFT in double
+                        precision with the key in 16-bit halves, which keeps
+                        the rounding of every product exact (both exact) */
 } fhe_launch_config;
 
 /* Times every shape on synthetic gate batches of width 1, 2, 4, ... up to
@@ -514,8 +517,8 @@ int fhe_ctx_timing_launches(fhe_ctx* ctx, fhe_launch_record* out, size_t max, si
 const char* fhe_last_error(void);
 
 /* Test entry: one CMux step of the blind rotation on explicit HOST data,
- * computed on `device` with the production kernels of NTT arithmetic `arith`
- * (0: Goldilocks prime, 1: two 28-bit primes and CRT; see fhe_launch_config):
+ * computed on `device` with the production kernels of arithmetic `arith`
+ * (0: Goldilocks NTT, 1: FFT; see fhe_launch_config):
  *   acc[2][N] <- acc + BK_i [x] (X^abar acc - acc),
  * bk_i: uint32 [2l][2][N] (coefficient domain, rows r = 2j + p). */
 int fhe_debug_cmux(int device, int arith, const uint32_t* bk_i, int32_t abar, uint32_t* acc);

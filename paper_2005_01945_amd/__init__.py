@@ -400,7 +400,7 @@ def fhe_ctx_set_graphs(ctx, enable):
 
 # Launch shapes of the blind-rotation kernel (the autotuner's search space):
 # (waves_per_gate, gates_per_group, arith), arith 0 = Goldilocks NTT,
-# 1 = two-prime NTT.
+# 1 = double-precision FFT.
 SHAPES = [(w, g, a) for a in (0, 1) for (w, g) in ((1, 1), (1, 2), (1, 4), (1, 8), (2, 1))] + [(4, 1, 1)]
 
 
@@ -537,7 +537,7 @@ def fhe_serve_stats(srv):
 
 
 def fhe_debug_cmux(bk_i, abar, acc, device=0, arith=0):
-    """One CMux step on host arrays with the production kernels of NTT
+    """One CMux step on host arrays with the production kernels of
     arithmetic `arith` (test entry)."""
     b, pb = _host(bk_i, np.uint32)
     a = np.ascontiguousarray(acc, np.uint32).copy()

@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "fft.h"
+
 namespace fhe {
 namespace dev {
 
@@ -53,28 +55,32 @@ struct DeviceKeys {
     const uint32_t* zero_row; // 512 zero words (digit 0 rows)
     const uint64_t* twf;      // forward twiddles [32][32]
     const uint64_t* twi;      // inverse twiddles (with N^-1) [32][32]
-    // Two-prime NTT: BK residues (Montgomery form, 32-bit words)
-    // [n][hp][prime][q / 2][64 lanes][q % 2][digit], and twiddle tables int32
-    // [prime][32][32] (8 KB each, read as 1024 uint64).
-    const uint64_t* bkq;
-    const uint64_t* twfq;
-    const uint64_t* twiq;
+    // FFT products: BK halves at the leaves in the two kernels' layouts (65.5
+    // MB each) and the roots E(k) = exp(i pi k / 1024), k < 2048.
+    const fft::cd* bkw;
+    const fft::cd* bkc;
+    const fft::cd* roots;
 };
+
+// Complex words of the FFT-domain key of one CMux: 4 rows x 4 outputs (column,
+// key half) x 512 leaves.
+constexpr int kKeyStep = 4 * 4 * 512;
 
 // BK (uint32 [n][2l][2][N], device) -> NTT-domain kernel layout.
 hipError_t launch_bk_prepare(const uint32_t* bk, uint64_t* bkd, const uint64_t* twf,
                              uint32_t n_lwe, hipStream_t s);
-// The same for the two-prime NTT (twfq: the two-prime forward table).
-hipError_t launch_bk_prepare_q(const uint32_t* bk, uint64_t* bkq, const uint64_t* twfq,
-                               uint32_t n_lwe, hipStream_t s);
+// The same to the FFT domain (either layout may be null).
+hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc, const fft::cd* roots,
+                                 uint32_t n_lwe, hipStream_t s);
 
-// Kernel shape of a blind-rotation launch.  waves_per_gate = 1: one wave
-// bootstraps a gate, gates_per_group in {1, 2, 4, 8} gates share a workgroup
-// (and its twiddle copy in LDS).  waves_per_gate = 2: two waves split each
-// CMux of one gate (one gate per workgroup; gates_per_group is ignored);
-// waves_per_gate = 4 (arith 1 only): one wave per (polynomial, prime).
-// arith: 0 = NTT over the Goldilocks prime, 1 = NTT modulo two 28-bit
-// primes recombined by CRT.  Every shape gives the same words.
+// Kernel shape of a blind-rotation launch.  arith: 0 = NTT over the Goldilocks
+// prime, 1 = double-precision FFT with the key in two halves.
+//   arith 0: waves_per_gate = 1: one wave bootstraps a gate, gates_per_group in
+//     {1, 2, 4, 8} gates share a workgroup (and its twiddle copy in LDS);
+//     waves_per_gate = 2: two waves split each CMux of one gate.
+//   arith 1: waves_per_gate = 1: groups of four gates on four waves, whatever
+//     gates_per_group; waves_per_gate = 2 or 4: that many waves per gate.
+// Every shape gives the same words.
 struct LaunchConfig {
     uint32_t waves_per_gate;
     uint32_t gates_per_group;
@@ -92,7 +98,7 @@ hipError_t launch_key_switch(const DeviceKeys& K, const GateIO& io, const uint32
                              uint32_t count, hipStream_t s);
 
 // One CMux on acc[2][N] (device) with prepared BK_i (one iteration of bkd
-// for arith 0, of bkq for arith 1).
+// for arith 0, of K.bkw for arith 1).
 hipError_t launch_debug_cmux(const DeviceKeys& K, int arith, const uint64_t* bk_i, int32_t abar,
                              uint32_t* acc, hipStream_t s);
 

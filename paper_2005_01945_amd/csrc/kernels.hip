@@ -1,23 +1,31 @@
 // gfx950 kernels of TFHE gate bootstrapping.
 //
-// Arithmetic: the negacyclic products of the CMux external product are done
-// as an exact NTT over Z_p, p = 2^64 - 2^32 + 1.  Digits are in [-512, 511]
-// and key words are read as signed 32-bit, so every coefficient of a summed
-// product is below 4 * 1024 * 2^9 * 2^31 = 2^52 < p/2 in magnitude and lifts
-// back to Z/2^32 exactly: results equal the schoolbook definition bit for bit.
+// CMux i (TFHE blind rotation): D = X^abar_i ACC - ACC; the two gadget digits
+// of its two polynomials (four digit rows) are multiplied by BK_i and summed
+// into the two columns of ACC, all modulo 2^32 and X^1024 + 1.  The negacyclic
+// products are exact in either of two arithmetics:
 //
-// Work layout: one wavefront (64 lanes) bootstraps one gate; its accumulator
-// (two polynomials of 1024 uint32) lives in LDS.  Lane l = 32h + t (half h,
-// t < 32) transforms polynomial data of coefficients m = t + 32*q, held in
-// register q (q < 32).  A 1024-point negacyclic
+//   arith 1 (default): complex FFTs of 512 points in double precision with the
+//   key words split in two 16-bit halves, which keeps every product
+//   coefficient below 2^36 and its rounding exact (the bound is in fft.h).
+//
+//   arith 0: an NTT over Z_p, p = 2^64 - 2^32 + 1.  Digits are in [-512, 511]
+//   and key words are read as signed 32-bit, so every coefficient of a summed
+//   product is below 4 * 1024 * 2^9 * 2^31 = 2^52 < p/2 in magnitude and lifts
+//   back to Z/2^32 exactly.
+//
+// Both equal the schoolbook definition bit for bit.
+//
+// Work layout of arith 0: one wavefront (64 lanes) bootstraps one gate; its
+// accumulator (two polynomials of 1024 uint32) lives in LDS.  Lane l = 32h + t
+// (half h, t < 32) transforms polynomial data of coefficients m = t + 32*q,
+// held in register q (q < 32).  A 1024-point negacyclic
 // NTT is split 32 x 32: a 32-point negacyclic transform in registers over q
 // (root psi^32 = 8, so every twiddle is a power of two: shifts only), one
 // general twiddle psi^(t(2j+1)) per value, a transpose through LDS, and a
 // 32-point cyclic transform in registers (root psi^64 = 2^6).  After it, lane
 // (h, t) register q holds frequency k = t + 32*brv5(q).  The inverse runs the
-// same steps backwards; N^-1 is folded into its twiddles.
-//
-// CMux i (TFHE blind rotation): D = X^abar_i ACC - ACC; each half extracts
+// same steps backwards; N^-1 is folded into its twiddles.  Each half extracts
 // its own gadget digit (half h -> digit h) of polynomial hp = 0, 1 in two
 // passes, transforms it, swaps it with the other half (v_permlane32_swap),
 // and half h accumulates output column h against BK_i in the NTT domain.
@@ -26,9 +34,9 @@
 #include <type_traits>
 
 #include "fhe_internal.h"
+#include "fft.h"
 #include "goldilocks.h"
 #include "kernels.h"
-#include "modq.h"
 
 namespace fhe {
 namespace dev {
@@ -154,30 +162,14 @@ __device__ __forceinline__ const lds_u32* lds_column(const uint32_t* a, int t) {
     return p;
 }
 
-// Gadget digit of coefficient m of D = X^ai ACC - ACC for this half (digit
-// h of two: bits 22..31 for h = 0, 12..21 for h = 1), in [-512, 511], from
-// d4 = 4 (m - ai).  d4 needs no reduction: its bits 2..11 are (m - ai) mod
-// 1024 times 4, the byte offset of the word read, and its bit 12 tells
-// whether (m - ai) mod 2048 >= 1024 (X^N = -1: the word is negated), for
-// negative m - ai too.  doff is the rounding offset of both digits plus
-// 2^(shift + 9), which makes the signed 10-bit field equal to the unsigned
-// field minus 512.
-__device__ __forceinline__ uint32_t digit_offset(int h) { return kDecompOffset + (1u << (31 - 10 * h)); }
-
-// The digit in two halves, so that the reads can run ahead of the digits:
-// the word's LDS address, with abase the byte address of the polynomial (a
-// multiple of 4096), is one AND-OR; the digit comes from the word v read
-// there and the unrotated word own.  The negation is written (v + sgn) ^
-// sgn, which needs the mask alone (the form (v ^ sgn) - sgn makes the
-// optimiser build -sgn as a second, zero-extended bit): bit-field extract,
-// add, XOR-add, subtract per coefficient.
+// Word of X^ai ACC's coefficient m before its sign, from d4 = 4 (m - ai) and
+// the polynomial's LDS byte address (a multiple of 4096).  d4 needs no
+// reduction: its bits 2..11 are (m - ai) mod 1024 times 4, the byte offset of
+// the word read (the address is one AND-OR), and its bit 12 tells whether
+// (m - ai) mod 2048 >= 1024 (X^N = -1: the word is negated), for negative
+// m - ai too.
 __device__ __forceinline__ uint32_t rotated_word(uint32_t abase, int d4) {
     return *(const lds_u32*)(uintptr_t)(((uint32_t)d4 & 0xFFCu) | abase);
-}
-
-__device__ __forceinline__ int32_t rotated_digit_q(uint32_t v, uint32_t own, int d4, uint32_t doff, int shift) {
-    const uint32_t sgn = (uint32_t)__builtin_amdgcn_sbfe(d4, 12, 1);
-    return __builtin_amdgcn_sbfe((int32_t)(((v + sgn) ^ sgn) + (doff - own)), shift, 10);
 }
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -252,58 +244,33 @@ __device__ __forceinline__ uint64_t partner64(uint64_t v, int h) {
 
 // Per-wave LDS, as views into the block's arrays: the accumulator (two
 // polynomials of 1024 words) and one 32 x 32 transpose tile of 32-bit words
-// per half (TW words: 32 x 32 with an XOR swizzle for the Goldilocks path,
-// 32 x 36 padded rows for the two-prime path).  16 KB (17 KB).
-template <int TW>
-struct WaveLdsT {
+// per half.  16 KB.
+struct WaveLds {
     uint32_t (&acc)[2][1024];
-    uint32_t (&tile)[2][TW];
+    uint32_t (&tile)[2][32 * 32];
 };
-using WaveLds = WaveLdsT<32 * 32>;
-
-template <int A>
-constexpr int kTileWords = A == 1 ? 32 * 36 : 32 * 32;
 
 // Shared-memory footprint of a block of WPB one-wave gates: twiddles plus one
-// accumulator and one pair of tiles per wave (WPB = 4 with the Goldilocks
-// path: 80 KB, so two blocks fit a CU's 160 KB, i.e. two waves per SIMD;
-// WPB = 8 with the two-prime path: 152 KB, one block of two waves per SIMD).
-// Every accumulator polynomial starts at a multiple of 4 KB (rotated_digit_q).
-template <int WPB, int A>
-struct alignas(4096) BlockLds {
+// accumulator and one pair of tiles per wave (WPB = 4: 80 KB, so two blocks
+// fit a CU's 160 KB, i.e. two waves per SIMD).
+template <int WPB>
+struct BlockLds {
     uint64_t twf[32 * 32];
     uint64_t twi[32 * 32];
     uint32_t acc[WPB][2][1024];
-    uint32_t tile[WPB][2][kTileWords<A>];
+    uint32_t tile[WPB][2][32 * 32];
 };
-using BlockLds81 = BlockLds<8, 1>;
-static_assert(offsetof(BlockLds81, acc) % 4096 == 0, "accumulators must be 4 KB aligned");
 
 // Shared memory of one gate bootstrapped by two waves (56 KB): wave w runs
 // pass w of every CMux; wave 1 hands its multiply-accumulate result to wave 0
 // through `part`, and wave 0 finishes the step.
-template <int A>
-struct alignas(4096) PairLds {
+struct PairLds {
     uint64_t twf[32 * 32];
     uint64_t twi[32 * 32];
     uint32_t acc[2][1024];
-    uint32_t tile[2][2][kTileWords<A>];  // [wave][half]
-    uint64_t part[32][64];               // [register q][lane]
+    uint32_t tile[2][2][32 * 32];  // [wave][half]
+    uint64_t part[32][64];         // [register q][lane]
 };
-static_assert(offsetof(PairLds<1>, acc) % 4096 == 0, "accumulators must be 4 KB aligned");
-
-// Shared memory of one gate bootstrapped by four waves (two-prime arithmetic
-// only, 74 KB): wave w = 2 hp + prime runs pass hp in that prime; the pass-1
-// waves hand their column sums to the pass-0 waves through `part`, which
-// finish their prime; wave 1 hands its residues to wave 0, which recombines.
-struct alignas(4096) QuadLds {
-    uint64_t twf[32 * 32];
-    uint64_t twi[32 * 32];
-    uint32_t acc[2][1024];
-    uint32_t tile[4][2][32 * 36];  // [wave][half]
-    int32_t part[2][32][64];       // [prime][register][lane]
-};
-static_assert(offsetof(QuadLds, acc) % 4096 == 0, "accumulators must be 4 KB aligned");
 
 // Pass HP of a CMux step: D = X^ai ACC_HP - ACC_HP (a = ACC_HP), this half's
 // gadget digit of it (half h extracts digit h), its forward NTT, then the
@@ -387,485 +354,236 @@ __device__ __forceinline__ void cmux_step(WaveLds& W, int ai, const uint64_t* __
 }
 
 // ---------------------------------------------------------------------------
-// The same CMux with the products computed modulo two 28-bit primes q0, q1
-// (modq.h) and recombined by the Chinese remainder theorem.  A 64-bit
-// multiply-accumulate value holds the prime-0 residue in its low word and the
-// prime-1 residue in its high word (signed 32-bit each); BK is in the
-// Montgomery form c R mod q with |c| <= q/2, in the 32-bit layout
-// [i][hp][prime][q / 2][lane 32c + t][q % 2][digit]: the four words of a
-// lane's register pair (2 registers x 2 digits) are one 16-byte load.
-// Twiddle tables (LDS, int32): forward [prime][q][t] = psi^(t(2 brv5(q)+1)) R,
-// inverse [prime][r][j] = psi^(-r(2j+1)) N^-1 R.
+// The same CMux with its products by complex FFTs in double precision (fft.h):
+// four digit rows r = 2 hp + digit forward, four outputs o = 2 c + half back
+// (column c, key half), 512 complex points each.
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ int32_t lo_of(uint64_t v) { return (int32_t)(uint32_t)v; }
-__device__ __forceinline__ int32_t hi_of(uint64_t v) { return (int32_t)(uint32_t)(v >> 32); }
-__device__ __forceinline__ uint64_t pack2(int32_t a, int32_t b) {
-    return ((uint64_t)(uint32_t)b << 32) | (uint32_t)a;
-}
+using fft::cd;
 
-// 32 x 32 transpose of 32-bit values through a tile of 32 rows of 36 words:
-// element (row, col) at row*36 + col.  Column writes hit 32 consecutive
-// words per row; each lane reads its row as eight 16-byte loads, and the
-// rows' 4-word skew spreads eight lanes' loads over all 32 banks.  Every
-// address is a per-lane base (t or 36 t) plus a constant, so no per-register
-// address is kept live.  Before: register k holds (row wr(k), col t); after:
-// register k holds (row t, col k).
-template <class WR>
-__device__ __forceinline__ void transpose32_w(int32_t (&x)[32], uint32_t* tile, int t, WR wr) {
-    uint32_t* col = tile + t;  // this lane's column
-    // This lane's row, as an LDS address opaque to the optimiser: otherwise
-    // it hoists one base address per pair of reads out of the CMux loop and
-    // spills them.  (Kept in the LDS address space so that the reads are LDS
-    // instructions, which wait on LDS traffic only.)
-    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(3))) v4u lds_u4;
-    lds_u4* row = (lds_u4*)(tile + 36 * t);
-    asm volatile("" : "+v"(row));
-    // LDS phases take the highest issue priority (the transforms have 1): a
-    // wave about to wait on LDS gets its requests out first, then the SIMD's
-    // other wave computes under the latency
-    __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-    for (int k = 0; k < 32; ++k) col[wr(k) * 36] = (uint32_t)x[k];
-    wave_lds_sync();
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-        const v4u v = row[g];
-        x[4 * g + 0] = (int32_t)v.x;
-        x[4 * g + 1] = (int32_t)v.y;
-        x[4 * g + 2] = (int32_t)v.z;
-        x[4 * g + 3] = (int32_t)v.w;
-    }
-    __builtin_amdgcn_s_setprio(0);
-    wave_lds_sync();
-}
+// Leaf and coefficient order of a transform on one wavefront (64 lanes x 8
+// registers, 512 = 8 x 8 x 8): coefficient j = lane + 64 reg before, leaf
+// p = 8 lane + reg after.  Between the passes the registers are exchanged with
+// the lanes' upper, then lower three bits through the wave's own 9 KB of LDS;
+// the strides of 72 and 9 sixteen-byte slots spread the sixteen lanes that
+// read together over all 64 banks.
+constexpr int kExSlots = 576;
 
-// x[B..B+8) *= w[0..8) (Montgomery forms), in three phases (products,
-// quotients, reductions) so that dependent instructions are 8 apart.
-template <int I, int B>
-__device__ __forceinline__ void mul8_q(int32_t (&x)[32], const int32_t (&w)[8]) {
-    int64_t p[8];
-    int32_t m[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) p[k] = (int64_t)x[B + k] * w[k];
-    sched_fence();
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m[k] = (int32_t)((uint32_t)p[k] * mq::Mod<I>::qinv);
-    sched_fence();
-#pragma unroll
-    for (int k = 0; k < 8; ++k) x[B + k] = (int32_t)((p[k] - (int64_t)m[k] * (int64_t)mq::Mod<I>::q) >> 32);
-    sched_fence();
-}
-
-// Table twiddles: x[q] *= tw[q * 32 + t], eight at a time.
-template <int I>
-__device__ __forceinline__ void table_mul_q(int32_t (&x)[32], const int32_t* tw, int t) {
-    int32_t w[2][8];  // the twiddles of chunk c + 1 are read before chunk c is multiplied
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w[0][k] = tw[k * 32 + t];
-    mq::static_for<0, 4>([&](auto C_) {
-        constexpr int c = decltype(C_)::value;
-        if constexpr (c < 3) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) w[(c + 1) & 1][k] = tw[(8 * c + 8 + k) * 32 + t];
-        }
-        mul8_q<I, 8 * c>(x, w[c & 1]);
-    });
-}
-
-// Forward 1024-point negacyclic NTT modulo q_I of this half's polynomial
-// (|x| < q in); lane t, register r then holds frequency t + 32 brv5(r),
-// bounded by 7 q.
-template <int I>
-__device__ __forceinline__ void ntt1024_fwd_q(int32_t (&x)[32], uint32_t* tile, const int32_t* twf, int t) {
-    mq::ntt32<I, mq::kNeg, 1>(x);
-    table_mul_q<I>(x, twf, t);
-    transpose32_w(x, tile, t, [](int q) { return brv5(q); });
-    mq::ntt32<I, mq::kCycFwd, 1>(x);
-}
-
-// Inverse, from the forward's layout with |x| < 2q: lane t, register r then
-// holds the residue (|.| < q) of coefficient t + 32 brv5(r).
-template <int I>
-__device__ __forceinline__ void ntt1024_inv_q(int32_t (&x)[32], uint32_t* tile, const int32_t* twi, int t) {
-    mq::ntt32<I, mq::kDitInv, 2>(x);
-    table_mul_q<I>(x, twi, t);
-    transpose32_w(x, tile, t, [](int r) { return r; });
-    mq::ntt32<I, mq::kCycInv, 1>(x);
-    // negacyclic twist psi^(-32 q) of output q = brv5(r): rho^(-q)
-    mq::static_for<0, 4>([&](auto C_) {
-        constexpr int c = decltype(C_)::value;
-        int32_t w[8];
-        mq::static_for<0, 8>([&](auto K_) {
-            constexpr int r = 8 * c + decltype(K_)::value;
-            w[decltype(K_)::value] = mq::sconst<mq::Mod<I>::rho.v[(64 - brv5(r)) % 64]>();
-        });
-        mul8_q<I, 8 * c>(x, w);
-    });
-}
-
-// Multiply-accumulate of prime I for pass HP: column h of the products of the
-// two digit transforms (r0: digit 0, half 0's; r1: digit 1, half 1's, both
-// obtained with one v_permlane32_swap) with BK rows 2HP and 2HP + 1.
-// bk: the prime-I plane of BK_i for pass HP, [q / 2][64 lanes][q % 2][digit] words, in
-// 8 chunks of 4 registers (8 words).  Key loads run W chunks ahead of their
-// use; the first W chunks (`pre`) were issued before the forward transform.
-template <int W>
-struct KeyWindow {
-    uint32_t w[W + 1 > 8 ? 8 : W + 1][8];
+// A lane's twiddles, held in registers across the rotation.
+struct LaneTwiddles {
+    cd f2[4], f3[4];  // forward passes 2 and 3
+    cd i2[4], i1[4];  // inverse passes 2 and 1 (conjugates)
 };
 
-template <int W>
-__device__ __forceinline__ void prefetch_q(const uint32_t* __restrict__ bk, int lane, KeyWindow<W>& kw) {
-#pragma unroll
-    for (int c = 0; c < W; ++c)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const uint4 v = *reinterpret_cast<const uint4*>(bk + ((2 * c + u) * 64 + lane) * 4);
-            kw.w[c][4 * u + 0] = v.x;
-            kw.w[c][4 * u + 1] = v.y;
-            kw.w[c][4 * u + 2] = v.z;
-            kw.w[c][4 * u + 3] = v.w;
-        }
+__device__ __forceinline__ cd conj_root(const cd* __restrict__ roots, int k) {
+    const cd e = roots[k & 2047];
+    return {e.x, -e.y};
 }
 
-template <int I, bool ACCUM, int W>
-__device__ __forceinline__ void mac_q(const int32_t (&x)[32], const uint32_t* __restrict__ bk,
-                                      KeyWindow<W>& kw, int lane, int32_t (&mac)[32]) {
-    constexpr int R = W + 1 > 8 ? 8 : W + 1;  // ring slots
-    mq::static_for<0, 8>([&](auto C_) {
-        constexpr int c = decltype(C_)::value;
-        if constexpr (c + W < 8) {
+__device__ __forceinline__ int brv3(int x) { return ((x & 1) << 2) | (x & 2) | ((x >> 2) & 1); }
+
+__device__ __forceinline__ void load_forward_twiddles(LaneTwiddles& W, const cd* __restrict__ roots, int lane) {
+    const int n2 = 32 + 128 * brv3(lane >> 3);
+    const int n3 = 4 + 16 * brv3(lane >> 3) + 128 * brv3(lane & 7);
+    W.f2[0] = roots[n2], W.f2[1] = roots[n2 / 2], W.f2[2] = roots[n2 / 4], W.f2[3] = roots[n2 / 4 + 256];
+    W.f3[0] = roots[n3], W.f3[1] = roots[n3 / 2], W.f3[2] = roots[n3 / 4], W.f3[3] = roots[n3 / 4 + 256];
+}
+
+__device__ __forceinline__ void load_inverse_twiddles(LaneTwiddles& W, const cd* __restrict__ roots, int lane) {
+    const int m0 = lane & 7;
+    W.i2[0] = conj_root(roots, 128 * m0), W.i2[1] = conj_root(roots, 64 * m0);
+    W.i2[2] = conj_root(roots, 32 * m0), W.i2[3] = conj_root(roots, 32 * m0 + 256);
+    W.i1[0] = conj_root(roots, 16 * lane), W.i1[1] = conj_root(roots, 8 * lane);
+    W.i1[2] = conj_root(roots, 4 * lane), W.i1[3] = conj_root(roots, 4 * lane + 256);
+}
+
+// Exchanges through the wave's slots: registers written at base + stride k,
+// read at base + stride k.
+template <int WS, int RS>
+__device__ __forceinline__ void wave_exchange(cd (&x)[8], cd* wbase, const cd* rbase) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const uint4 v = *reinterpret_cast<const uint4*>(bk + ((2 * (c + W) + u) * 64 + lane) * 4);
-                kw.w[(c + W) % R][4 * u + 0] = v.x;
-                kw.w[(c + W) % R][4 * u + 1] = v.y;
-                kw.w[(c + W) % R][4 * u + 2] = v.z;
-                kw.w[(c + W) % R][4 * u + 3] = v.w;
+    for (int k = 0; k < 8; ++k) wbase[WS * k] = x[k];
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = rbase[RS * k];
+    wave_lds_sync();
+}
+
+__device__ __forceinline__ void fft512_forward(cd (&x)[8], cd* ex, const LaneTwiddles& W, int lane) {
+    const int hi = lane >> 3, lo = lane & 7;
+    fft::forward_root<8>(x);
+    wave_exchange<72, 8>(x, ex + lane, ex + hi * 72 + lo);
+    fft::forward_lane<8>(x, [&](auto k) { return W.f2[decltype(k)::value]; });
+    wave_exchange<9, 1>(x, ex + hi * 72 + lo, ex + hi * 72 + 9 * lo);
+    fft::forward_lane<8>(x, [&](auto k) { return W.f3[decltype(k)::value]; });
+}
+
+// Inverse of the above without the factor 1/512, which the key carries, and
+// without the twist (finish_words applies it).
+__device__ __forceinline__ void fft512_inverse(cd (&x)[8], cd* ex, const LaneTwiddles& W, int lane) {
+    const int hi = lane >> 3, lo = lane & 7;
+    fft::inverse_root<8>(x);
+    wave_exchange<1, 9>(x, ex + hi * 72 + 9 * lo, ex + hi * 72 + lo);
+    fft::inverse_lane8(x, W.i2);
+    wave_exchange<8, 72>(x, ex + hi * 72 + lo, ex + lane);
+    fft::inverse_lane8(x, W.i1);
+}
+
+// Twist (tw: LDS table of the 512 factors) and rounding: word e (0..15) of
+// coefficient lane + 64 e.
+__device__ __forceinline__ void finish_words(const cd (&x)[8], const cd* tw, int lane, uint32_t (&v)[16]) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const cd t = tw[64 * q + lane];
+        v[q] = fft::round_word(__builtin_fma(t.x, x[q].x, -(t.y * x[q].y)));
+        v[q + 8] = fft::round_word(__builtin_fma(t.x, x[q].y, t.y * x[q].x));
+    }
+}
+
+// D = X^ai ACC - ACC plus the rounding offset of both digits, of coefficient
+// m with d4 = 4 (m - ai) (see rotated_word), with the top bit of each digit's
+// field flipped so that the signed 10-bit fields at 22 and 12 are the digits.
+__device__ __forceinline__ uint32_t digit_word(uint32_t v, uint32_t own, int d4) {
+    uint32_t sgn;  // (the optimiser would turn the bit-field extract into a compare and a select)
+    asm("v_bfe_i32 %0, %1, 12, 1" : "=v"(sgn) : "v"(d4));
+    return (((v + sgn) ^ sgn) + (kDecompOffset - own)) ^ 0x80200000u;
+}
+
+// Digit rows of polynomial a: coefficient lane + 64 e, e < 8 real, else
+// imaginary part of register e mod 8.  ND = 2: both digits; ND = 1: the digit
+// whose field starts at bit `shift`.
+template <int ND>
+__device__ __forceinline__ void wave_digits(const uint32_t* a, int ai, int shift, int lane, cd (&x)[ND][8]) {
+    const lds_u32* am = lds_column(a, lane);
+    const uint32_t abase = (uint32_t)(uintptr_t)(const lds_u32*)a;
+    const int d4 = 4 * (lane - ai);
+    uint32_t v[16], own[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        v[e] = rotated_word(abase, d4 + 256 * e);
+        own[e] = am[64 * e];
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const uint32_t z = digit_word(v[e], own[e], d4 + 256 * e);
+#pragma unroll
+        for (int d = 0; d < ND; ++d) {
+            const double dg = (double)(int32_t)__builtin_amdgcn_sbfe((int32_t)z, ND == 2 ? 22 - 10 * d : shift, 10);
+            if (e < 8)
+                x[d][e & 7].x = dg;
+            else
+                x[d][e & 7].y = dg;
+        }
+    }
+}
+
+__device__ __forceinline__ void mac(cd& o, const cd& k, const cd& x) {
+    o.x = __builtin_fma(-k.y, x.y, __builtin_fma(k.x, x.x, o.x));
+    o.y = __builtin_fma(k.y, x.x, __builtin_fma(k.x, x.y, o.y));
+}
+
+// Barrier for data exchanged through LDS alone: key loads in flight stay in
+// flight (__syncthreads would wait for them).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ __forceinline__ void lds_add(uint32_t* p, uint32_t v) {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// LDS of a gate on W wavefronts: accumulator, each wave's exchange slots, the
+// twist factors and the digit spectra that the waves share.
+template <int W>
+struct alignas(4096) FftLds {
+    uint32_t acc[2][1024];
+    cd ex[W][kExSlots];
+    cd tw[512];
+    cd spec[4][512];
+};
+
+// Key word of row r, output o, register j, lane (wave layout).
+__device__ __forceinline__ const cd* key_row(const cd* __restrict__ key, int r, int o, int lane) {
+    return key + ((r * 4 + o) * 8) * 64 + lane;
+}
+
+// Keys of a gate on four wavefronts: the wave's whole share of a step (rows x
+// registers), each row reloaded for the next step as soon as it is used.
+struct KeyAhead {
+    cd row[4][8];
+};
+
+__device__ __forceinline__ void load_key_row(cd (&k)[8], const cd* __restrict__ key, int r, int o, int lane) {
+    const cd* p = key_row(key, r, o, lane);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) k[j] = p[64 * j];
+}
+
+// One CMux step of a gate on W = 2 or 4 wavefronts.  Wave w transforms rows
+// (4 / W) w ... and finishes outputs (4 / W) w ...; the rows' spectra meet in
+// LDS.  Two barriers per step: spectra written, ACC updated.  With W = 4 the
+// step's keys are in `ka` and those of the next step (next) are loaded.
+template <int W>
+__device__ __forceinline__ void fft_step(FftLds<W>& S, int ai, const cd* __restrict__ key, const cd* __restrict__ next,
+                                         KeyAhead& ka, const LaneTwiddles& T, int wave, int lane) {
+    constexpr int RP = 4 / W;
+    uint32_t (&acc)[2][1024] = S.acc;
+    cd* ex = S.ex[wave];
+    cd pre[RP][2][8];  // W = 2: keys of rows 0 and 1, on their way during the transforms
+    if constexpr (W == 2) {
+#pragma unroll
+        for (int k = 0; k < RP; ++k)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) load_key_row(pre[k][r], key, r, RP * wave + k, lane);
+        sched_fence();
+    }
+    cd x[RP][8];
+    if constexpr (W == 4)
+        wave_digits<1>(acc[wave >> 1], ai, 22 - 10 * (wave & 1), lane, x);
+    else
+        wave_digits<2>(acc[wave], ai, 0, lane, x);
+#pragma unroll
+    for (int k = 0; k < RP; ++k) {
+        fft512_forward(x[k], ex, T, lane);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) S.spec[RP * wave + k][64 * j + lane] = x[k][j];
+    }
+    lds_barrier();  // spectra written; every wave has read ACC
+    cd out[RP][8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const cd v = S.spec[r][64 * j + lane];
+#pragma unroll
+            for (int k = 0; k < RP; ++k) {
+                if (r == 0) out[k][j] = {0.0, 0.0};
+                mac(out[k][j],
+                    W == 4 ? ka.row[r][j] : r < 2 ? pre[k][r & 1][j] : key_row(key, r, RP * wave + k, lane)[64 * j], v);
             }
         }
-        sched_fence();
-        // phases: exchanges, first products, second products, quotients,
-        // reductions (dependent instructions four apart)
-        int32_t d0[4], d1[4], m[4];
-        int64_t p[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)x[4 * c + j], (uint32_t)x[4 * c + j], false, false);
-            d0[j] = (int32_t)sw[0];
-            d1[j] = (int32_t)sw[1];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) p[j] = (int64_t)d0[j] * (int32_t)kw.w[c % R][2 * j];
-        sched_fence();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) p[j] += (int64_t)d1[j] * (int32_t)kw.w[c % R][2 * j + 1];
-        sched_fence();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) m[j] = (int32_t)((uint32_t)p[j] * mq::Mod<I>::qinv);
-        sched_fence();
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int32_t v = (int32_t)((p[j] - (int64_t)m[j] * (int64_t)mq::Mod<I>::q) >> 32);
-            mac[4 * c + j] = ACCUM ? mac[4 * c + j] + v : v;
-        }
-    });
-    sched_fence();
-}
-
-// Pass HP of a CMux step with two-prime products (see cmux_pass): digits of
-// ACC_HP (half h: digit h), then for each prime in turn its transform and
-// multiply-accumulate of column h.  The digits wait for the second prime
-// packed two to a register.  mac: low word prime 0, high word prime 1, each
-// |.| < q per pass.  bk_i: BK_i, [hp][prime][q / 2][64 lanes][q % 2][digit] words.
-// W: key-load window in chunks (8: all loads issued before the transform).
-template <int HP, bool ACCUM, int W>
-__device__ __forceinline__ void cmux_pass_q(const uint32_t* a, uint32_t* tile, int ai,
-                                            const uint64_t* __restrict__ bk_i, const int32_t* twf,
-                                            int lane, uint64_t (&mac)[32]) {
-    const int h = lane >> 5, t = lane & 31;
-    const int shift = 22 - 10 * h;
-    const uint32_t doff = digit_offset(h);
-    const lds_u32* am = lds_column(a, t);
-    const uint32_t abase = (uint32_t)(uintptr_t)(const lds_u32*)a;
-    int d4 = 4 * (t - ai);  // opaque: each pass forms its own addresses instead of keeping them
-    asm volatile("" : "+v"(d4));
-    const uint32_t* bk0 = reinterpret_cast<const uint32_t*>(bk_i) + HP * 8192;
-    const uint32_t* bk1 = bk0 + 4096;
-    KeyWindow<W> kw;
-    prefetch_q<W>(bk0, lane, kw);
-    int32_t x[32];
-    uint32_t dp[16];
-    // the reads of chunk c + 1 are issued before the digits of chunk c
-    uint32_t rv[2][8], ow[2][8];
-    int dq[2][8];
-    auto issue = [&](auto C_, auto B_) {
-        constexpr int c = decltype(C_)::value, b = decltype(B_)::value;
-        __builtin_amdgcn_s_setprio(2);  // as in transpose32_w
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int q = 8 * c + k;
-            dq[b][k] = d4 + 128 * q;
-            rv[b][k] = rotated_word(abase, dq[b][k]);
-            ow[b][k] = am[32 * q];
-        }
-        __builtin_amdgcn_s_setprio(0);
-    };
-    issue(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
-    mq::static_for<0, 4>([&](auto C_) {
-        constexpr int c = decltype(C_)::value;
-        sched_fence();
-        if constexpr (c < 3) issue(std::integral_constant<int, c + 1>{}, std::integral_constant<int, (c + 1) & 1>{});
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int q = 8 * c + k;
-            x[q] = rotated_digit_q(rv[c & 1][k], ow[c & 1][k], dq[c & 1][k], doff, shift);
-        }
-#pragma unroll
-        for (int j = 4 * c; j < 4 * c + 4; ++j)
-            dp[j] = ((uint32_t)x[2 * j] & 0xFFFFu) | ((uint32_t)x[2 * j + 1] << 16);
-    });
-    sched_fence();
-    int32_t m0[32], m1[32];
-    if constexpr (ACCUM) {
-#pragma unroll
-        for (int q = 0; q < 32; ++q) {
-            m0[q] = lo_of(mac[q]);
-            m1[q] = hi_of(mac[q]);
+        if constexpr (W == 4) {
+            load_key_row(ka.row[r], next, r, wave, lane);
+            sched_fence();
         }
     }
-    ntt1024_fwd_q<0>(x, tile, twf, t);
-    mac_q<0, ACCUM, W>(x, bk0, kw, lane, m0);
-    prefetch_q<W>(bk1, lane, kw);
+    uint32_t v[RP][16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        x[2 * j] = (int32_t)(dp[j] << 16) >> 16;
-        x[2 * j + 1] = (int32_t)dp[j] >> 16;
+    for (int k = 0; k < RP; ++k) {
+        fft512_inverse(out[k], ex, T, lane);
+        finish_words(out[k], S.tw, lane, v[k]);
     }
-    ntt1024_fwd_q<1>(x, tile, twf + 1024, t);
-    mac_q<1, ACCUM, W>(x, bk1, kw, lane, m1);
+    if constexpr (W == 4) {
 #pragma unroll
-    for (int q = 0; q < 32; ++q) mac[q] = pack2(m0[q], m1[q]);
+        for (int e = 0; e < 16; ++e) lds_add(&acc[wave >> 1][lane + 64 * e], v[0][e] << (16 * (wave & 1)));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) lds_add(&acc[wave][lane + 64 * e], v[0][e] + (v[RP - 1][e] << 16));
+    }
+    lds_barrier();  // ACC updated; spectra free
 }
-
-// Inverse NTTs of both columns (half h: column h), CRT, ACC += result.
-// One prime's share of pass HP (the four-wave shape): the digits of ACC_HP,
-// their transform modulo q_I and the multiply-accumulate of column h.
-template <int HP, int I, int W>
-__device__ __forceinline__ void cmux_pass_q1(const uint32_t* a, uint32_t* tile, int ai,
-                                             const uint64_t* __restrict__ bk_i, const int32_t* twf,
-                                             int lane, int32_t (&mac)[32]) {
-    const int h = lane >> 5, t = lane & 31;
-    const int shift = 22 - 10 * h;
-    const uint32_t doff = digit_offset(h);
-    const lds_u32* am = lds_column(a, t);
-    const uint32_t abase = (uint32_t)(uintptr_t)(const lds_u32*)a;
-    int d4 = 4 * (t - ai);  // opaque: the pass forms its own addresses instead of keeping them
-    asm volatile("" : "+v"(d4));
-    const uint32_t* bk = reinterpret_cast<const uint32_t*>(bk_i) + HP * 8192 + I * 4096;
-    KeyWindow<W> kw;
-    prefetch_q<W>(bk, lane, kw);
-    int32_t x[32];
-    // the reads of chunk c + 1 are issued before the digits of chunk c
-    uint32_t rv[2][8], ow[2][8];
-    int dq[2][8];
-    auto issue = [&](auto C_, auto B_) {
-        constexpr int c = decltype(C_)::value, b = decltype(B_)::value;
-        __builtin_amdgcn_s_setprio(2);  // as in transpose32_w
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int q = 8 * c + k;
-            dq[b][k] = d4 + 128 * q;
-            rv[b][k] = rotated_word(abase, dq[b][k]);
-            ow[b][k] = am[32 * q];
-        }
-        __builtin_amdgcn_s_setprio(0);
-    };
-    issue(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
-    mq::static_for<0, 4>([&](auto C_) {
-        constexpr int c = decltype(C_)::value;
-        sched_fence();
-        if constexpr (c < 3) issue(std::integral_constant<int, c + 1>{}, std::integral_constant<int, (c + 1) & 1>{});
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int q = 8 * c + k;
-            x[q] = rotated_digit_q(rv[c & 1][k], ow[c & 1][k], dq[c & 1][k], doff, shift);
-        }
-    });
-    sched_fence();
-    ntt1024_fwd_q<I>(x, tile, twf + I * 1024, t);
-    mac_q<I, false, W>(x, bk, kw, lane, mac);
-}
-
-__device__ __forceinline__ void crt_update_q(uint32_t (&acc)[2][1024], const int32_t (&x0)[32],
-                                             const int32_t (&x1)[32], int lane);
-
-__device__ __forceinline__ void cmux_finish_q(uint32_t (&acc)[2][1024], uint32_t* tile,
-                                              uint64_t (&mac)[32], const int32_t* twi, int lane) {
-    const int t = lane & 31;
-    int32_t x0[32], x1[32];
-#pragma unroll
-    for (int q = 0; q < 32; ++q) {
-        x0[q] = lo_of(mac[q]);
-        x1[q] = hi_of(mac[q]);
-    }
-    ntt1024_inv_q<0>(x0, tile, twi, t);
-    ntt1024_inv_q<1>(x1, tile, twi + 1024, t);
-    crt_update_q(acc, x0, x1, lane);
-}
-
-// ACC (half h: polynomial h) += the column given by its residues x0, x1
-// (register r: coefficient t + 32 brv5(r)).
-// Registers 8C..8C+7 of the CRT update below (x0, x1: those registers'
-// residues; old: their accumulator words, read ahead by the caller).  The
-// constants come in scalar registers (crt_consts), so that
-// the optimiser keeps the products as multiplies instead of expanding them
-// into shifts and adds of the 2^28 - 2^16 + ... forms of the primes.
-struct CrtConsts {
-    int32_t q0, nq1, cq;  // q0, -q1, q0^-1 R mod q1 (centred)
-};
-
-__device__ __forceinline__ CrtConsts crt_consts() {
-    constexpr int32_t cq = mq::Mod<1>::rform(mq::powmod(mq::Mod<0>::q, mq::Mod<1>::q - 2, mq::Mod<1>::q));
-    return {mq::sconst<(int32_t)mq::Mod<0>::q>(), mq::sconst<-(int32_t)mq::Mod<1>::q>(), mq::sconst<cq>()};
-}
-
-template <int C>
-__device__ __forceinline__ void crt_chunk_core(uint32_t (&acc)[2][1024], const int32_t (&x0)[8],
-                                               const int32_t (&x1)[8], int lane, const CrtConsts& K,
-                                               const uint32_t (&old)[8]) {
-    const int h = lane >> 5, t = lane & 31;
-    uint32_t* mine = acc[h] + t;
-    int32_t d[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        d[k] = x1[k];
-        asm volatile("" : "+v"(d[k]));  // keeps the subtraction 32-bit (the optimiser folds it into
-        d[k] -= x0[k];                    // the preceding Montgomery reduction as a 64-bit one)
-    }
-    sched_fence();
-    int64_t p[8];
-    int32_t m[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) p[k] = (int64_t)d[k] * K.cq;
-    sched_fence();
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m[k] = (int32_t)((uint32_t)p[k] * mq::Mod<1>::qinv);
-    sched_fence();
-#pragma unroll
-    for (int k = 0; k < 8; ++k) d[k] = (int32_t)((p[k] + (int64_t)m[k] * K.nq1) >> 32);
-    sched_fence();
-#pragma unroll
-    for (int k = 0; k < 8; ++k) mine[32 * brv5(8 * C + k)] = old[k] + (uint32_t)x0[k] + (uint32_t)K.q0 * (uint32_t)d[k];
-    sched_fence();
-}
-
-// The same, reading the chunk's accumulator words itself.
-template <int C>
-__device__ __forceinline__ void crt_chunk_q(uint32_t (&acc)[2][1024], const int32_t (&x0)[8],
-                                            const int32_t (&x1)[8], int lane, const CrtConsts& K) {
-    const uint32_t* mine = acc[lane >> 5] + (lane & 31);
-    uint32_t old[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) old[k] = mine[32 * brv5(8 * C + k)];
-    crt_chunk_core<C>(acc, x0, x1, lane, K, old);
-}
-
-// Residues (|v0| < q0, |v1| < q1) of an integer V with |V| <= 2^52 ->
-// V mod 2^32: V = v0 + q0 T with T = (v1 - v0) q0^-1 mod q1 taken in
-// (-q1/2, q1/2); in fact |T| <= (2^52 + q0) / q0 < 2^24 + 2^13.  The Montgomery
-// product t = mont((v1 - v0) cq), cq = q0^-1 R mod q1 centred, is that T
-// without any correction: |v1 - v0| < 2^29 and |cq| <= q1/2 < 2^27 bound the
-// product by 2^56, so |t| < 2^56 / 2^32 + q1/2 < 2^24 + q1/2, and t and T,
-// congruent modulo q1, differ by less than 2^25 + 2^13 + q1/2 < q1: t = T.
-// ACC[h][t + 32 brv5(r)] += V.  Eight registers at a time, in phases.
-__device__ __forceinline__ void crt_update_q(uint32_t (&acc)[2][1024], const int32_t (&x0)[32],
-                                             const int32_t (&x1)[32], int lane) {
-    const CrtConsts K = crt_consts();
-    const uint32_t* mine = acc[lane >> 5] + (lane & 31);
-    uint32_t old[2][8];  // the words of chunk c + 1 are read before chunk c is updated
-#pragma unroll
-    for (int k = 0; k < 8; ++k) old[0][k] = mine[32 * brv5(k)];
-    mq::static_for<0, 4>([&](auto C_) {
-        constexpr int c = decltype(C_)::value;
-        if constexpr (c < 3) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) old[(c + 1) & 1][k] = mine[32 * brv5(8 * c + 8 + k)];
-        }
-        int32_t a0[8], a1[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            a0[k] = x0[8 * c + k];
-            a1[k] = x1[8 * c + k];
-        }
-        crt_chunk_core<c>(acc, a0, a1, lane, K, old[c & 1]);
-    });
-}
-
-template <int KW>
-__device__ __forceinline__ void cmux_step_q(WaveLdsT<32 * 36>& W, int ai, const uint64_t* __restrict__ bk_i,
-                                            const int32_t* twf, const int32_t* twi, int lane) {
-    const int h = lane >> 5;
-    uint64_t mac[32];
-    cmux_pass_q<0, false, KW>(W.acc[0], W.tile[h], ai, bk_i, twf, lane, mac);
-    cmux_pass_q<1, true, KW>(W.acc[1], W.tile[h], ai, bk_i, twf, lane, mac);
-    cmux_finish_q(W.acc, W.tile[h], mac, twi, lane);
-    wave_lds_sync();
-}
-
-// Arithmetic selector of the blind-rotation kernels: 0 = Goldilocks NTT,
-// 1 = two-prime NTT.
-template <int A>
-struct Arith;
-
-template <>
-struct Arith<0> {
-    __host__ __device__ static const uint64_t* bk(const DeviceKeys& K) { return K.bkd; }
-    __host__ __device__ static const uint64_t* twf(const DeviceKeys& K) { return K.twf; }
-    __host__ __device__ static const uint64_t* twi(const DeviceKeys& K) { return K.twi; }
-    template <int KW>
-    __device__ __forceinline__ static void step(WaveLds& W, int ai, const uint64_t* bk_i, const uint64_t* twf,
-                                const uint64_t* twi, int lane) {
-        cmux_step(W, ai, bk_i, twf, twi, lane);
-    }
-    template <int HP, int KW>
-    __device__ __forceinline__ static void pass(const uint32_t* a, uint32_t* tile, int ai, const uint64_t* bk_i,
-                                const uint64_t* twf, int lane, uint64_t (&mac)[32]) {
-        cmux_pass<HP, false, true>(a, tile, ai, bk_i, twf, lane, mac);  // (two-wave shape only)
-    }
-    __device__ __forceinline__ static uint64_t add(uint64_t x, uint64_t y) { return gl::add(x, y); }
-    __device__ __forceinline__ static void finish(uint32_t (&acc)[2][1024], uint32_t* tile, uint64_t (&mac)[32],
-                                  const uint64_t* twi, int lane) {
-        cmux_finish(acc, tile, mac, twi, lane);
-    }
-};
-
-template <>
-struct Arith<1> {
-    __host__ __device__ static const uint64_t* bk(const DeviceKeys& K) { return K.bkq; }
-    __host__ __device__ static const uint64_t* twf(const DeviceKeys& K) { return K.twfq; }
-    __host__ __device__ static const uint64_t* twi(const DeviceKeys& K) { return K.twiq; }
-    template <int KW>
-    __device__ __forceinline__ static void step(WaveLdsT<32 * 36>& W, int ai, const uint64_t* bk_i, const uint64_t* twf,
-                                const uint64_t* twi, int lane) {
-        cmux_step_q<KW>(W, ai, bk_i, reinterpret_cast<const int32_t*>(twf),
-                    reinterpret_cast<const int32_t*>(twi), lane);
-    }
-    template <int HP, int KW>
-    __device__ __forceinline__ static void pass(const uint32_t* a, uint32_t* tile, int ai, const uint64_t* bk_i,
-                                const uint64_t* twf, int lane, uint64_t (&mac)[32]) {
-        cmux_pass_q<HP, false, KW>(a, tile, ai, bk_i, reinterpret_cast<const int32_t*>(twf), lane, mac);
-    }
-    __device__ __forceinline__ static uint64_t add(uint64_t x, uint64_t y) {
-        return pack2(lo_of(x) + lo_of(y), hi_of(x) + hi_of(y));
-    }
-    __device__ __forceinline__ static void finish(uint32_t (&acc)[2][1024], uint32_t* tile, uint64_t (&mac)[32],
-                                  const uint64_t* twi, int lane) {
-        cmux_finish_q(acc, tile, mac, reinterpret_cast<const int32_t*>(twi), lane);
-    }
-};
 
 // Gate constants: phase offset kappa and input signs (TFHE +-1/8 encoding)
 // of the two-input codes 0..9.
@@ -966,6 +684,12 @@ __device__ __forceinline__ uint32_t* ks_output(const GateIO& io, uint32_t k) {
     if ((k & 1) == 0) return gate_output(io, g);
     if (io.desc) return (io.desc[g].x & kCompoundFlag) ? wire_ptr(io, io.desc3[g]) : nullptr;
     return io.ops1 ? io.out1 + (size_t)g * NW : nullptr;
+}
+
+template <int THREADS>
+__device__ __forceinline__ void load_twist(cd* tw, const cd* __restrict__ roots) {
+    for (int k = threadIdx.x; k < 512; k += THREADS) tw[k] = conj_root(roots, k);
+    __syncthreads();
 }
 
 template <int THREADS, class L>
@@ -1102,19 +826,14 @@ __device__ __forceinline__ void gate_epilogue(const GateIO& io, uint32_t g, cons
 // Kernels.
 // ---------------------------------------------------------------------------
 
-// Key-load window (chunks of 8 words ahead) of the two-prime passes.  Two
-// chunks measured best for every shape: issuing all of a pass's key loads
-// before its transform was slower even with the full register file.
-constexpr int kKeyWindow = 2;
-
 // Gate linear combination + modulus switch, test-vector rotation, 500 CMux,
 // sample extraction.  One wave per gate, WPB gates per block; the register
 // budget allows two waves per SIMD.
-template <int WPB, int A>
+template <int WPB>
 __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_blind_rotate(
     DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
-    __shared__ BlockLds<WPB, A> S;
-    load_twiddles<64 * WPB>(S, Arith<A>::twf(K), Arith<A>::twi(K));
+    __shared__ BlockLds<WPB> S;
+    load_twiddles<64 * WPB>(S, K.twf, K.twi);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const uint32_t g = blockIdx.x * WPB + wave;
     if (g >= count) return;
@@ -1122,17 +841,17 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int h = lane >> 5, t = lane & 31;
     uint32_t ab[8];
     const int bbar = gate_prologue(io, g, lane, ab);
-    WaveLdsT<kTileWords<A>> W{S.acc[wave], S.tile[wave]};
+    WaveLds W{S.acc[wave], S.tile[wave]};
     acc_init(W.acc, bbar, h, t, io.tv, gate_mu(io, g));
     wave_lds_sync();
 
     // Blind rotation.  abar_i = 0 would give D = 0 and leave ACC unchanged,
     // so every step runs unconditionally.
-    const uint64_t* bk = Arith<A>::bk(K);
+    const uint64_t* bk = K.bkd;
 #pragma unroll 1
     for (int i = 0; i < NLWE; ++i) {
         const int ai = __builtin_amdgcn_readlane(ab[0], i & 63);
-        Arith<A>::template step<kKeyWindow>(W, ai, bk, S.twf, S.twi, lane);
+        cmux_step(W, ai, bk, S.twf, S.twi, lane);
         bk += 2 * 32 * 2 * 64;
         if ((i & 63) == 63) {
 #pragma unroll
@@ -1148,11 +867,10 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(2, 2))
 // partial sums, runs the inverse NTTs and updates ACC while wave 1 waits.
 // The critical path of a CMux drops from two passes plus the inverse to one
 // pass plus the inverse; the issued work stays the same.
-template <int A>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_blind_rotate_pair(
     DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
-    __shared__ PairLds<A> S;
-    load_twiddles<128>(S, Arith<A>::twf(K), Arith<A>::twi(K));
+    __shared__ PairLds S;
+    load_twiddles<128>(S, K.twf, K.twi);
     const uint32_t g = blockIdx.x;
     if (g >= count) return;  // uniform over the block
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1163,103 +881,23 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     if (wave == 0) acc_init(S.acc, bbar, h, t, io.tv, gate_mu(io, g));
     __syncthreads();
 
-    const uint64_t* bk = Arith<A>::bk(K);
-    if constexpr (A == 1) {
-        // Two-prime form: each wave also takes one prime's inverse.  The
-        // waves swap the other prime's partial column sums, wave w
-        // finishes prime w, the waves swap the residues of half of the
-        // registers, and wave w recombines and updates registers 16w..16w+15.
-        int32_t* part0 = reinterpret_cast<int32_t*>(&S.part[0][0]);  // [32][64]
-        int32_t* part1 = part0 + 32 * 64;
-        const int32_t* twi = reinterpret_cast<const int32_t*>(S.twi);
-#pragma unroll 1
-        for (int i = 0; i < NLWE; ++i) {
-            const int ai = __builtin_amdgcn_readlane(ab[0], i & 63);
-            uint64_t mac[32];
-            int32_t x[32];
-            if (wave == 0) {
-                Arith<A>::template pass<0, kKeyWindow>(S.acc[0], S.tile[0][h], ai, bk, S.twf, lane, mac);
-#pragma unroll
-                for (int q = 0; q < 32; ++q) part1[q * 64 + lane] = hi_of(mac[q]);
-            } else {
-                Arith<A>::template pass<1, kKeyWindow>(S.acc[1], S.tile[1][h], ai, bk, S.twf, lane, mac);
-#pragma unroll
-                for (int q = 0; q < 32; ++q) part0[q * 64 + lane] = lo_of(mac[q]);
-            }
-            __syncthreads();  // partials written; both waves done reading ACC
-            if (wave == 0) {
-#pragma unroll
-                for (int q = 0; q < 32; ++q) x[q] = lo_of(mac[q]) + part0[q * 64 + lane];
-                ntt1024_inv_q<0>(x, S.tile[0][h], twi, t);
-            } else {
-#pragma unroll
-                for (int q = 0; q < 32; ++q) x[q] = hi_of(mac[q]) + part1[q * 64 + lane];
-                ntt1024_inv_q<1>(x, S.tile[1][h], twi + 1024, t);
-            }
-            // wave 0 hands over prime-0 residues of registers 16..31, wave 1
-            // prime-1 residues of registers 0..15 (each read its slot above)
-            {
-                int32_t* mine = wave == 0 ? part0 : part1;
-                const int r0 = wave == 0 ? 16 : 0;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mine[(r0 + r) * 64 + lane] = x[r0 + r];
-            }
-            __syncthreads();  // residues written
-            if (wave == 0) {
-                int32_t a0[8], a1[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    a0[k] = x[k];
-                    a1[k] = part1[k * 64 + lane];
-                }
-                crt_chunk_q<0>(S.acc, a0, a1, lane, crt_consts());
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    a0[k] = x[8 + k];
-                    a1[k] = part1[(8 + k) * 64 + lane];
-                }
-                crt_chunk_q<1>(S.acc, a0, a1, lane, crt_consts());
-            } else {
-                int32_t a0[8], a1[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    a0[k] = part0[(16 + k) * 64 + lane];
-                    a1[k] = x[16 + k];
-                }
-                crt_chunk_q<2>(S.acc, a0, a1, lane, crt_consts());
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    a0[k] = part0[(24 + k) * 64 + lane];
-                    a1[k] = x[24 + k];
-                }
-                crt_chunk_q<3>(S.acc, a0, a1, lane, crt_consts());
-            }
-            __syncthreads();  // ACC updated
-            bk += 2 * 32 * 2 * 64;
-            if ((i & 63) == 63) {
-#pragma unroll
-                for (int r = 0; r < 7; ++r) ab[r] = ab[r + 1];
-            }
-        }
-        gate_epilogue<128>(io, g, S.acc, big, threadIdx.x);
-        return;
-    }
+    const uint64_t* bk = K.bkd;
 #pragma unroll 1
     for (int i = 0; i < NLWE; ++i) {
         const int ai = __builtin_amdgcn_readlane(ab[0], i & 63);
         uint64_t mac[32];
         if (wave == 0) {
-            Arith<A>::template pass<0, kKeyWindow>(S.acc[0], S.tile[0][h], ai, bk, S.twf, lane, mac);
+            cmux_pass<0, false, true>(S.acc[0], S.tile[0][h], ai, bk, S.twf, lane, mac);
         } else {
-            Arith<A>::template pass<1, kKeyWindow>(S.acc[1], S.tile[1][h], ai, bk, S.twf, lane, mac);
+            cmux_pass<1, false, true>(S.acc[1], S.tile[1][h], ai, bk, S.twf, lane, mac);
 #pragma unroll
             for (int q = 0; q < 32; ++q) S.part[q][lane] = mac[q];
         }
         __syncthreads();  // part written; both waves done reading ACC
         if (wave == 0) {
 #pragma unroll
-            for (int q = 0; q < 32; ++q) mac[q] = Arith<A>::add(mac[q], S.part[q][lane]);
-            Arith<A>::finish(S.acc, S.tile[0][h], mac, S.twi, lane);
+            for (int q = 0; q < 32; ++q) mac[q] = gl::add(mac[q], S.part[q][lane]);
+            cmux_finish(S.acc, S.tile[0][h], mac, S.twi, lane);
         }
         __syncthreads();  // ACC updated; part free
         bk += 2 * 32 * 2 * 64;
@@ -1271,78 +909,304 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     gate_epilogue<128>(io, g, S.acc, big, threadIdx.x);
 }
 
-// Four waves per gate (two-prime arithmetic), for the lowest latency: the
-// critical path of a CMux is one prime's pass, one prime's inverse and the
-// recombination.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_blind_rotate_quad(
-    DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
-    __shared__ QuadLds S;
-    load_twiddles<256>(S, K.twfq, K.twiq);
-    const uint32_t g = blockIdx.x;
-    if (g >= count) return;  // uniform over the block
+// Blind rotation with FFT products, W = 2 or 4 wavefronts per gate, for
+// batches that leave compute units with one gate or two.  Bound by latency:
+// at one gate per compute unit a CMux step takes 4.4 us (W = 4) for 830 VALU
+// instructions per wave, about 40% of the issue rate; the rest is the LDS
+// exchanges and two barriers.  With W = 4 the key words of a step are loaded
+// one whole step ahead into 128 registers (loading half of them at the start
+// of the step and half after the transforms: 7.8 us), so this shape runs one
+// wave per SIMD.  256 gates: 2.2 ms with W = 4, 2.7 ms with W = 2; 512 gates:
+// 4.4 ms and 3.0 ms (the integer NTTs modulo two primes that this replaces:
+// 3.3 ms at 256, 4.6 ms at 512).
+template <int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(1, W == 4 ? 1 : 2)))
+void k_blind_rotate_fft(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
+    __shared__ FftLds<W> S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, h = lane >> 5, t = lane & 31;
-
+    load_twist<64 * W>(S.tw, K.roots);
+    const uint32_t g = blockIdx.x;
+    if (g >= count) return;  // uniform over the block
+    LaneTwiddles T;
+    load_forward_twiddles(T, K.roots, lane);
+    load_inverse_twiddles(T, K.roots, lane);
     uint32_t ab[8];
     const int bbar = gate_prologue(io, g, lane, ab);
     if (wave == 0) acc_init(S.acc, bbar, h, t, io.tv, gate_mu(io, g));
+    const cd* key = K.bkw;
+    KeyAhead ka;
+    if constexpr (W == 4) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) load_key_row(ka.row[r], key, r, wave, lane);
+    }
     __syncthreads();
-
-    const int32_t* twf = reinterpret_cast<const int32_t*>(S.twf);
-    const int32_t* twi = reinterpret_cast<const int32_t*>(S.twi);
-    const uint64_t* bk = K.bkq;
 #pragma unroll 1
     for (int i = 0; i < NLWE; ++i) {
         const int ai = __builtin_amdgcn_readlane(ab[0], i & 63);
-        int32_t x[32];
-        uint32_t* tile = S.tile[wave][h];
-        switch (wave) {
-        case 0: cmux_pass_q1<0, 0, kKeyWindow>(S.acc[0], tile, ai, bk, twf, lane, x); break;
-        case 1: cmux_pass_q1<0, 1, kKeyWindow>(S.acc[0], tile, ai, bk, twf, lane, x); break;
-        case 2: cmux_pass_q1<1, 0, kKeyWindow>(S.acc[1], tile, ai, bk, twf, lane, x); break;
-        default: cmux_pass_q1<1, 1, kKeyWindow>(S.acc[1], tile, ai, bk, twf, lane, x); break;
-        }
-        if (wave >= 2) {
-#pragma unroll
-            for (int q = 0; q < 32; ++q) S.part[wave - 2][q][lane] = x[q];
-        }
-        __syncthreads();  // pass-1 sums written; all waves done reading ACC
-        if (wave < 2) {  // wave p: prime p's column sums, inverse transform
-#pragma unroll
-            for (int q = 0; q < 32; ++q) x[q] += S.part[wave][q][lane];
-            if (wave == 0)
-                ntt1024_inv_q<0>(x, tile, twi, t);
-            else
-                ntt1024_inv_q<1>(x, tile, twi + 1024, t);
-            // residues of the registers the other waves recombine (this wave
-            // read its part[] slot above)
-#pragma unroll
-            for (int r = 0; r < 32; ++r)
-                if (r / 8 != wave) S.part[wave][r][lane] = x[r];
-        }
-        __syncthreads();  // residues written
-        {  // wave w recombines registers 8w..8w+7
-            int32_t a0[8], a1[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                a0[k] = wave == 0 ? x[k] : S.part[0][8 * wave + k][lane];
-                a1[k] = wave == 1 ? x[8 + k] : S.part[1][8 * wave + k][lane];
-            }
-            switch (wave) {
-            case 0: crt_chunk_q<0>(S.acc, a0, a1, lane, crt_consts()); break;
-            case 1: crt_chunk_q<1>(S.acc, a0, a1, lane, crt_consts()); break;
-            case 2: crt_chunk_q<2>(S.acc, a0, a1, lane, crt_consts()); break;
-            default: crt_chunk_q<3>(S.acc, a0, a1, lane, crt_consts()); break;
-            }
-        }
-        __syncthreads();  // ACC updated
-        bk += 2 * 32 * 2 * 64;
+        const cd* next = i + 1 < NLWE ? key + kKeyStep : key;
+        fft_step<W>(S, ai, key, next, ka, T, wave, lane);
+        key = next;
         if ((i & 63) == 63) {
 #pragma unroll
             for (int r = 0; r < 7; ++r) ab[r] = ab[r + 1];
         }
     }
-    gate_epilogue<256>(io, g, S.acc, big, threadIdx.x);
+    gate_epilogue<64 * W>(io, g, S.acc, big, threadIdx.x);
+}
+
+// Blind rotation with FFT products for wide batches: groups of four gates on
+// four wavefronts.  Wave w extracts and finishes gate w, and in between holds
+// a quarter of the spectrum of all four gates, so that each key value loaded
+// serves four gates (a wave per gate would stream 128 KB of key per step and
+// gate through a 64 B per clock cache, more than half the time of the
+// arithmetic) and the multiply-add over the rows is a matrix product.  The f64
+// matrix instructions run at the rate of the VALU and not beside it: they
+// save exchanges, not arithmetic.
+// Lane layouts (32 complex registers):
+//   A: lane (polynomial hp or column c, t): registers (digit or half, q),
+//      coefficient pair t + 32 q of gate w;
+//   B: lane (row r or output o, b, gate n): registers t, node Q = 4 w + b of
+//      the first four levels (block Q of 32 leaves).
+// 512 = 16 x 32 points need one exchange between them, through LDS, first all
+// real, then all imaginary parts (64 KB, so that two groups fit a compute
+// unit): value (Q, r, n, t) in row 64 (Q / 4) + 16 r + 4 (Q % 4) + n, column t.
+// Between the steps the accumulators are in registers and pass through the
+// same LDS to be read rotated.
+//
+// Bound by issue: about 2,360 VALU (1,860 of them f64 at 4.5-4.9 cycles) and
+// 128 matrix instructions of 16 cycles per wave and step, 13,000 of the 16,800
+// cycles that a step takes per wave at two waves per SIMD.  16,384 gates in
+// 54 ms, 2,048 in 7.4 ms, 1,024 (one wave per SIMD) in 4.8 ms; the integer
+// NTTs modulo two 28-bit primes that this replaces issued 6,570 VALU per wave
+// and step: 100, 12.5 and 8.1 ms.
+constexpr int kRowBytes = 32 * 8 + 16;  // 16-byte skew: lanes of layout B read 16 rows at once
+
+struct alignas(4096) GroupLds {
+    char buf[256 * kRowBytes];  // also the accumulators (8 KB per wave) during the extraction
+    cd tabf[16][16];            // twiddle k of block Q (forward levels 5..9)
+    cd tabi[32][16];            // inverse factor of coefficient t, block Q
+};
+static_assert(2 * sizeof(GroupLds) <= 160 * 1024, "two groups per compute unit");
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
+    __shared__ GroupLds S;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, h = lane >> 5, t = lane & 31;
+    {
+        const int Q = threadIdx.x & 15, f = threadIdx.x >> 4;  // twiddle f: level l, even node c = 2 d
+        const int l = f == 0 ? 0 : f == 1 ? 1 : f < 4 ? 2 : f < 8 ? 3 : 4;
+        const int d = f < 2 ? 0 : f - (1 << (l - 1));
+        int s = 0;  // c_0 + 2 c_1 + ... of the l - 1 leading path bits
+        for (int b = 0; b < l - 1; ++b) s |= ((d >> (l - 2 - b)) & 1) << b;
+        const int n = 16 + 64 * fft::brv(Q, 4);
+        S.tabf[f][Q] = K.roots[((n >> l) + (1024 >> l) * s) & 2047];
+    }
+    for (int k = threadIdx.x; k < 512; k += 256) {
+        const int Q = k & 15, m = k >> 4;
+        S.tabi[m][Q] = conj_root(K.roots, m * (1 + 4 * fft::brv(Q, 4)));
+    }
+    char* buf = S.buf;
+    uint32_t (&accl)[2][1024] = *reinterpret_cast<uint32_t (*)[2][1024]>(buf + 8192 * w);
+    const uint32_t g = blockIdx.x * 4 + w;
+    const bool live = g < count;  // a missing gate's wave still serves the others' spectrum
+    uint32_t ab[8] = {}, acc[32] = {};
+    if (live) {
+        const int bbar = gate_prologue(io, g, lane, ab);
+        acc_init(accl, bbar, h, t, io.tv, gate_mu(io, g));
+        wave_lds_sync();
+#pragma unroll
+        for (int e = 0; e < 32; ++e) acc[e] = accl[h][t + 32 * e];
+    }
+    __syncthreads();
+
+    const int b = (lane >> 2) & 3;
+    char* colA = buf + (32 * h + w) * kRowBytes + 8 * t;       // layout A: this lane's column
+    char* rowB = buf + (64 * w + lane) * kRowBytes;            // layout B: this lane's row
+    const cd* tf = &S.tabf[0][4 * w + b];
+    const cd* ti = &S.tabi[0][4 * w + b];
+    const cd* key = K.bkc + 64 * w + lane;
+    const uint32_t abase = (uint32_t)(uintptr_t)(const lds_u32*)accl[h];
+    auto col_at = [&](auto d, auto q) -> double& {
+        constexpr int Q = decltype(q)::value;
+        return *reinterpret_cast<double*>(colA + (64 * (Q >> 2) + 16 * decltype(d)::value + 4 * (Q & 3)) * kRowBytes);
+    };
+#pragma unroll 1
+    for (int i = 0; i < NLWE; ++i) {
+        const int ai = __builtin_amdgcn_readlane(ab[0], i & 63);
+        cd x[2][16], y[32];
+        // digits of D = X^ai ACC - ACC, both of each coefficient
+#pragma unroll
+        for (int e = 0; e < 32; ++e) accl[h][t + 32 * e] = acc[e];
+        wave_lds_sync();
+        {
+            const int d4 = 4 * (t - ai);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                uint32_t v[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) v[k] = rotated_word(abase, d4 + 128 * (16 * c + k));
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    const uint32_t z = digit_word(v[k], acc[16 * c + k], d4 + 128 * (16 * c + k));
+#pragma unroll
+                    for (int d = 0; d < 2; ++d) {
+                        const double dg = (double)(int32_t)__builtin_amdgcn_sbfe((int32_t)z, 22 - 10 * d, 10);
+                        if (c == 0)
+                            x[d][k].x = dg;
+                        else
+                            x[d][k].y = dg;
+                    }
+                }
+            }
+        }
+        fft::forward_root<16>(x[0]);
+        fft::forward_root<16>(x[1]);
+        lds_barrier();  // every wave has read its accumulator
+        static_for<0, 2>([&](auto d) { static_for<0, 16>([&](auto q) { col_at(d, q) = x[d][q].x; }); });
+        lds_barrier();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const cd v = *reinterpret_cast<const cd*>(rowB + 16 * k);
+            y[2 * k].x = v.x;
+            y[2 * k + 1].x = v.y;
+        }
+        lds_barrier();
+        static_for<0, 2>([&](auto d) { static_for<0, 16>([&](auto q) { col_at(d, q) = x[d][q].y; }); });
+        lds_barrier();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const cd v = *reinterpret_cast<const cd*>(rowB + 16 * k);
+            y[2 * k].y = v.x;
+            y[2 * k + 1].y = v.y;
+        }
+        constexpr int KW = 4;  // key loads in flight
+        cd kb[KW];
+#pragma unroll
+        for (int k = 0; k < KW; ++k) kb[k] = key[k * 256];
+        sched_fence();
+        fft::forward_lane<32>(y, [&](auto k) { return tf[16 * decltype(k)::value]; });
+        // out_o = sum over rows of K_(r, o) x_r, per leaf: matrix products of
+        // 4 outputs x 4 rows x 4 gates, four leaves (b) per instruction
+#pragma unroll
+        for (int c = 0; c < 32; c += 4) {
+            double re[4], im[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[(c + k) % KW].x, y[c + k].x, 0.0, 0, 0, 0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[(c + k) % KW].x, y[c + k].y, 0.0, 0, 0, 0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[(c + k) % KW].y, y[c + k].y, re[k], 0, 0, 1);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[(c + k) % KW].y, y[c + k].x, im[k], 0, 0, 0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                y[c + k] = {re[k], im[k]};
+                if (c + k + KW < 32) kb[(c + k) % KW] = key[(c + k + KW) * 256];
+            }
+            sched_fence();
+        }
+        key += kKeyStep;
+        fft::inverse_root<32>(y);
+#pragma unroll
+        for (int m = 1; m < 32; ++m) {
+            const cd f = ti[16 * m];
+            y[m] = {__builtin_fma(f.x, y[m].x, -(f.y * y[m].y)), __builtin_fma(f.x, y[m].y, f.y * y[m].x)};
+        }
+        lds_barrier();  // every wave has read the imaginary parts
+#pragma unroll
+        for (int k = 0; k < 16; ++k) *reinterpret_cast<cd*>(rowB + 16 * k) = {y[2 * k].x, y[2 * k + 1].x};
+        lds_barrier();
+        static_for<0, 2>([&](auto d) { static_for<0, 16>([&](auto q) { x[d][q].x = col_at(d, q); }); });
+        lds_barrier();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) *reinterpret_cast<cd*>(rowB + 16 * k) = {y[2 * k].y, y[2 * k + 1].y};
+        lds_barrier();
+        static_for<0, 2>([&](auto d) { static_for<0, 16>([&](auto q) { x[d][q].y = col_at(d, q); }); });
+        fft::inverse_root<16>(x[0]);
+        fft::inverse_root<16>(x[1]);
+        static_for<0, 16>([&](auto q_) {
+            constexpr int q = decltype(q_)::value;
+            constexpr double cr = fft::cos32(q), ci = -fft::sin32(q);  // twist of coefficient pair t + 32 q
+            uint32_t re[2], im[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const cd v = x[s][q];
+                re[s] = fft::round_word(q == 0 ? v.x : __builtin_fma(cr, v.x, -(ci * v.y)));
+                im[s] = fft::round_word(q == 0 ? v.y : __builtin_fma(cr, v.y, ci * v.x));
+            }
+            acc[q] += re[0] + (re[1] << 16);
+            acc[q + 16] += im[0] + (im[1] << 16);
+        });
+        lds_barrier();  // every wave has read its imaginary parts
+        if ((i & 63) == 63) {
+#pragma unroll
+            for (int r = 0; r < 7; ++r) ab[r] = ab[r + 1];
+        }
+    }
+    if (!live) return;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) accl[h][t + 32 * e] = acc[e];
+    wave_lds_sync();
+    gate_epilogue<64>(io, g, accl, big, lane);
+}
+
+// BK -> the FFT domain, scaled by 1/512 (the inverse transform's factor; a
+// power of two, exact), in both layouts: one wave per polynomial (CMux i, row
+// r, column c) transforms its low and its high signed half words.
+//   bkw[i][r][o][reg][lane] (k_blind_rotate_fft), leaf 8 lane + reg;
+//   bkc[i][leaf % 32][leaf / 128][16 r + 4 (leaf / 32 % 4) + o] (k_blind_rotate_group).
+__global__ __launch_bounds__(kBlockThreads) void k_bk_prepare_fft(const uint32_t* __restrict__ bk, cd* __restrict__ bkw,
+                                                                  cd* __restrict__ bkc, const cd* __restrict__ roots,
+                                                                  uint32_t npolys) {
+    __shared__ cd ex[kWavesPerBlock][kExSlots];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint32_t poly = blockIdx.x * kWavesPerBlock + wave;
+    if (poly >= npolys) return;
+    LaneTwiddles T;
+    load_forward_twiddles(T, roots, lane);
+    const uint32_t i = poly / 8, r = (poly / 2) % 4, c = poly % 2;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        cd x[8];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const uint32_t k = bk[(size_t)poly * N + lane + 64 * e];
+            const int32_t lo = (int16_t)k, hi = (int32_t)(k - (uint32_t)lo) >> 16;
+            const double v = s == 0 ? lo : hi;
+            if (e < 8)
+                x[e & 7].x = v;
+            else
+                x[e & 7].y = v;
+        }
+        fft512_forward(x, ex[wave], T, lane);
+        const uint32_t o = 2 * c + s;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const cd v = {x[j].x * (1.0 / 512), x[j].y * (1.0 / 512)};
+            const uint32_t leaf = 8 * lane + j;
+            if (bkw) bkw[(size_t)i * kKeyStep + ((r * 4 + o) * 8 + j) * 64 + lane] = v;
+            if (bkc) bkc[(size_t)i * kKeyStep + ((leaf % 32) * 4 + leaf / 128) * 64 + 16 * r + 4 * (leaf / 32 % 4) + o] = v;
+        }
+    }
+}
+
+// One CMux on acc[2][N] in global memory with the FFT products (four waves).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void k_debug_cmux_fft(DeviceKeys K, int32_t abar, uint32_t* __restrict__ accg) {
+    __shared__ FftLds<4> S;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    LaneTwiddles T;
+    load_forward_twiddles(T, K.roots, lane);
+    load_inverse_twiddles(T, K.roots, lane);
+    KeyAhead ka;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) load_key_row(ka.row[r], K.bkw, r, wave, lane);
+    for (int k = threadIdx.x; k < 2 * N; k += 256) S.acc[k / N][k % N] = accg[k];
+    load_twist<256>(S.tw, K.roots);
+    fft_step<4>(S, abar, K.bkw, K.bkw, ka, T, wave, lane);
+    for (int k = threadIdx.x; k < 2 * N; k += 256) accg[k] = S.acc[k / N][k % N];
 }
 
 // Key switching N -> n: out = (0, b') - sum_{i,j} KSK[i][j][d_ij], d_ij the
@@ -1478,72 +1342,18 @@ __global__ __launch_bounds__(kBlockThreads) void k_bk_prepare(const uint32_t* __
     for (int q = 0; q < 32; ++q) dst[(q * 2 + sel) * 64] = gl::canon(x[q]);
 }
 
-// BK -> two-prime NTT domain in the layout cmux_pass_q reads:
-// bkq[i][hp][prime][q / 2][lane 32c + t][q % 2][digit] (32-bit words) for row
-// r = 2hp + digit, column c, each residue in Montgomery form and centred
-// (|.| <= q/2).
-template <int I>
-__device__ __forceinline__ void bk_residue(const uint32_t* __restrict__ bk, uint32_t poly, int t,
-                                           int32_t (&x)[32], uint32_t* tile, const int32_t* twf) {
-    constexpr int64_t Q = mq::Mod<I>::q;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-        int64_t v = (int64_t)(int32_t)bk[(size_t)poly * N + t + 32 * k] % Q;  // |v| < q
-        x[k] = (int32_t)v;
-    }
-    ntt1024_fwd_q<I>(x, tile, twf, t);
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-        int32_t y = mq::mul<I>(x[k], mq::Mod<I>::rform(mq::Mod<I>::R % Q));  // x R, |.| < q
-        y += y < -(int32_t)(Q / 2) ? (int32_t)Q : 0;
-        y -= y > (int32_t)(Q / 2) ? (int32_t)Q : 0;
-        x[k] = y;
-    }
-}
-
-__global__ __launch_bounds__(kBlockThreads) void k_bk_prepare_q(const uint32_t* __restrict__ bk,
-                                                                uint64_t* __restrict__ bkq,
-                                                                const uint64_t* __restrict__ twfq,
-                                                                uint32_t npolys) {
-    __shared__ int32_t stw[2 * 32 * 32];
-    __shared__ uint32_t tiles[kWavesPerBlock][2][kTileWords<1>];
-    const int32_t* tw = reinterpret_cast<const int32_t*>(twfq);
-    for (int k = threadIdx.x; k < 2048; k += kBlockThreads) stw[k] = tw[k];
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int h = lane >> 5, t = lane & 31;
-    const uint32_t base = 2 * (blockIdx.x * kWavesPerBlock + wave);
-    if (base >= npolys) return;
-    const uint32_t poly = base + h;  // npolys is even
-    int32_t x0[32], x1[32];
-    bk_residue<0>(bk, poly, t, x0, &tiles[wave][h][0], stw);
-    bk_residue<1>(bk, poly, t, x1, &tiles[wave][h][0], stw + 1024);
-    const uint32_t i = poly / 8, r = (poly / 2) % 4, c = poly % 2;
-    const uint32_t hp = r >> 1, digit = r & 1;
-    uint32_t* dst = reinterpret_cast<uint32_t*>(bkq) + (size_t)i * 16384 + (size_t)hp * 8192;
-    const int lw = 32 * c + t;
-#pragma unroll
-    for (int q = 0; q < 32; ++q) {
-        dst[((q >> 1) * 64 + lw) * 4 + (q & 1) * 2 + digit] = (uint32_t)x0[q];
-        dst[4096 + ((q >> 1) * 64 + lw) * 4 + (q & 1) * 2 + digit] = (uint32_t)x1[q];
-    }
-}
-
-// One CMux on acc[2][N] in global memory (single wave).
-template <int A>
+// One CMux on acc[2][N] in global memory with the NTT products (single wave).
 __global__ __launch_bounds__(64) void k_debug_cmux(DeviceKeys K, const uint64_t* __restrict__ bk_i,
                                                    int32_t abar, uint32_t* __restrict__ accg) {
-    __shared__ BlockLds<1, A> S;
-    WaveLdsT<kTileWords<A>> W{S.acc[0], S.tile[0]};
-    const uint64_t* twf = Arith<A>::twf(K);
-    const uint64_t* twi = Arith<A>::twi(K);
+    __shared__ BlockLds<1> S;
+    WaveLds W{S.acc[0], S.tile[0]};
     for (int k = threadIdx.x; k < 1024; k += 64) {
-        S.twf[k] = twf[k];
-        S.twi[k] = twi[k];
+        S.twf[k] = K.twf[k];
+        S.twi[k] = K.twi[k];
     }
     for (int k = threadIdx.x; k < 2 * N; k += 64) W.acc[k / N][k % N] = accg[k];
     __syncthreads();
-    Arith<A>::template step<kKeyWindow>(W, abar, bk_i, S.twf, S.twi, threadIdx.x);
+    cmux_step(W, abar, bk_i, S.twf, S.twi, threadIdx.x);
     __syncthreads();
     for (int k = threadIdx.x; k < 2 * N; k += 64) accg[k] = W.acc[k / N][k % N];
 }
@@ -1609,40 +1419,34 @@ hipError_t launch_bk_prepare(const uint32_t* bk, uint64_t* bkd, const uint64_t* 
     return hipGetLastError();
 }
 
-template <int A>
-static hipError_t launch_blind_rotate_a(const DeviceKeys& K, const GateIO& io, uint32_t* big,
-                                        uint32_t count, LaunchConfig cfg, hipStream_t s) {
-    if (cfg.waves_per_gate == 2) {
-        hipLaunchKernelGGL(k_blind_rotate_pair<A>, dim3(count), dim3(128), 0, s, K, io, big, count);
-        return hipGetLastError();
-    }
-    const uint32_t wpb = cfg.gates_per_group;
-    const uint32_t blocks = (count + wpb - 1) / wpb;
-    switch (wpb) {
-    case 1: hipLaunchKernelGGL((k_blind_rotate<1, A>), dim3(blocks), dim3(64), 0, s, K, io, big, count); break;
-    case 2: hipLaunchKernelGGL((k_blind_rotate<2, A>), dim3(blocks), dim3(128), 0, s, K, io, big, count); break;
-    case 4: hipLaunchKernelGGL((k_blind_rotate<4, A>), dim3(blocks), dim3(256), 0, s, K, io, big, count); break;
-    case 8: hipLaunchKernelGGL((k_blind_rotate<8, A>), dim3(blocks), dim3(512), 0, s, K, io, big, count); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
+// Arithmetic 1 with one wave per gate always runs groups of four gates: the
+// share of the key loads that a smaller group would lose costs more than its
+// idle waves (one gate: 4.8 ms in a group, 18.7 ms on a wave by itself).
 hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* big,
                                uint32_t count, LaunchConfig cfg, hipStream_t s) {
     if (count == 0) return hipSuccess;
-    if (cfg.waves_per_gate == 4) {
-        if (cfg.arith != 1 || !K.bkq) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_blind_rotate_quad, dim3(count), dim3(256), 0, s, K, io, big, count);
+    auto launch = [&](auto kernel, uint32_t gates, uint32_t threads) {
+        hipLaunchKernelGGL(kernel, dim3((count + gates - 1) / gates), dim3(threads), 0, s, K, io, big, count);
         return hipGetLastError();
-    }
-    if (cfg.waves_per_gate != 1 && cfg.waves_per_gate != 2) return hipErrorInvalidValue;
+    };
     if (cfg.arith == 1) {
-        if (!K.bkq) return hipErrorInvalidValue;
-        return launch_blind_rotate_a<1>(K, io, big, count, cfg, s);
+        switch (cfg.waves_per_gate) {
+        case 1: return launch(k_blind_rotate_group, 4, 256);
+        case 2: return launch(k_blind_rotate_fft<2>, 1, 128);
+        case 4: return launch(k_blind_rotate_fft<4>, 1, 256);
+        default: return hipErrorInvalidValue;
+        }
     }
     if (cfg.arith != 0) return hipErrorInvalidValue;
-    return launch_blind_rotate_a<0>(K, io, big, count, cfg, s);
+    if (cfg.waves_per_gate == 2) return launch(k_blind_rotate_pair, 1, 128);
+    if (cfg.waves_per_gate != 1) return hipErrorInvalidValue;
+    switch (cfg.gates_per_group) {
+    case 1: return launch(k_blind_rotate<1>, 1, 64);
+    case 2: return launch(k_blind_rotate<2>, 2, 128);
+    case 4: return launch(k_blind_rotate<4>, 4, 256);
+    case 8: return launch(k_blind_rotate<8>, 8, 512);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_key_switch(const DeviceKeys& K, const GateIO& io, const uint32_t* big,
@@ -1664,18 +1468,17 @@ hipError_t launch_key_switch(const DeviceKeys& K, const GateIO& io, const uint32
 hipError_t launch_debug_cmux(const DeviceKeys& K, int arith, const uint64_t* bk_i, int32_t abar,
                              uint32_t* acc, hipStream_t s) {
     if (arith == 1)
-        hipLaunchKernelGGL(k_debug_cmux<1>, dim3(1), dim3(64), 0, s, K, bk_i, abar, acc);
+        hipLaunchKernelGGL(k_debug_cmux_fft, dim3(1), dim3(256), 0, s, K, abar, acc);
     else
-        hipLaunchKernelGGL(k_debug_cmux<0>, dim3(1), dim3(64), 0, s, K, bk_i, abar, acc);
+        hipLaunchKernelGGL(k_debug_cmux, dim3(1), dim3(64), 0, s, K, bk_i, abar, acc);
     return hipGetLastError();
 }
 
-hipError_t launch_bk_prepare_q(const uint32_t* bk, uint64_t* bkq, const uint64_t* twfq,
-                               uint32_t n_lwe, hipStream_t s) {
+hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc, const fft::cd* roots,
+                                 uint32_t n_lwe, hipStream_t s) {
     const uint32_t npolys = n_lwe * 8;
-    const uint32_t waves = npolys / 2;
-    const uint32_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-    hipLaunchKernelGGL(k_bk_prepare_q, dim3(blocks), dim3(kBlockThreads), 0, s, bk, bkq, twfq, npolys);
+    const uint32_t blocks = (npolys + kWavesPerBlock - 1) / kWavesPerBlock;
+    hipLaunchKernelGGL(k_bk_prepare_fft, dim3(blocks), dim3(kBlockThreads), 0, s, bk, bkw, bkc, roots, npolys);
     return hipGetLastError();
 }
 

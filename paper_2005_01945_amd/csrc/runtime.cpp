@@ -1,19 +1,20 @@
 // Device context and gate-bootstrapping entry points.
 //
 // A context keeps the cloud key resident on one GPU: the bootstrapping key
-// converted once to the NTT domain (32.8 MB), the key-switching key laid out
-// as 2 KB rows (50.3 MB), and the twiddle tables.  Gate batches run as two
+// converted once to the FFT domain (two layouts of 65.5 MB) and to the NTT
+// domain (32.8 MB), the key-switching key laid out as 2 KB rows (50.3 MB), and
+// the twiddle tables.  Gate batches run as two
 // launches on the caller's stream: blind rotation (with the gate prologue and
 // sample extraction fused in) and key switching.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <mutex>
 
 #include "fhe_internal.h"
 #include "goldilocks.h"
 #include "kernels.h"
 #include "runtime.h"
-#include "modq.h"
 
 namespace fhe {
 
@@ -51,24 +52,24 @@ void make_twiddles(std::vector<uint64_t>& twf, std::vector<uint64_t>& twi) {
         }
 }
 
-// Two-prime tables, int32 [prime][32][32] in Montgomery form: forward
-// psi^(t(2 brv5(q)+1)) at [q][t], inverse psi^(-r(2j+1)) N^-1 at [r][j].
-template <int I>
-static void make_twiddles_q1(int32_t* twf, int32_t* twi) {
-    using M = mq::Mod<I>;
-    const uint64_t ninv = mq::powmod(kN, M::q - 2, M::q);
-    for (int q = 0; q < 32; ++q)
-        for (int t = 0; t < 32; ++t) {
-            twf[q * 32 + t] = M::rform(M::psi_pow((int64_t)t * (2 * brv5h(q) + 1)));
-            twi[q * 32 + t] = M::rform(M::psi_pow(-(int64_t)q * (2 * t + 1)) * ninv % M::q);
-        }
-}
-
-void make_twiddles_q(std::vector<int32_t>& twf, std::vector<int32_t>& twi) {
-    twf.assign(2048, 0);
-    twi.assign(2048, 0);
-    make_twiddles_q1<0>(twf.data(), twi.data());
-    make_twiddles_q1<1>(twf.data() + 1024, twi.data() + 1024);
+// The 2048-th roots of unity exp(i pi k / 1024), each component the correctly
+// rounded value of one first-octant sine or cosine (in extended precision), so
+// that the symmetries between them hold exactly.
+void make_roots(std::vector<dev::fft::cd>& roots) {
+    const long double pi = 3.141592653589793238462643383279502884L;
+    auto cos_at = [&](int k) {  // cos(pi k / 1024), 0 <= k <= 512
+        return (double)(k <= 256 ? cosl(pi * k / 1024) : sinl(pi * (512 - k) / 1024));
+    };
+    roots.resize(2048);
+    for (int k = 0; k <= 512; ++k) {
+        const double c = cos_at(k), s = cos_at(512 - k);
+        roots[k] = {c, s};
+        roots[1024 - k] = {-c, s};
+        roots[(1024 + k) % 2048] = {-c, -s};
+        roots[(2048 - k) % 2048] = {c, -s};
+    }
+    roots[0] = {1.0, 0.0};
+    roots[1024] = {-1.0, 0.0};
 }
 
 DeviceGuard::DeviceGuard(int dev) {
@@ -216,8 +217,8 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
 
     std::vector<uint64_t> twf, twi;
     make_twiddles(twf, twi);
-    std::vector<int32_t> twfq, twiq;
-    make_twiddles_q(twfq, twiq);
+    std::vector<dev::fft::cd> roots;
+    make_roots(roots);
     const size_t n = ck->P.n, N = ck->P.N;
     const size_t bk_words = n * 4 * 2 * N;
     const size_t bkd_words = n * 2 * 32 * 2 * 64;
@@ -253,16 +254,20 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
     if ((e = hipMalloc((void**)&ctx->twf, 1024 * 8)) != hipSuccess) return fail(e, "twiddles");
     if ((e = hipMalloc((void**)&ctx->twi, 1024 * 8)) != hipSuccess) return fail(e, "twiddles");
     if ((e = hipMalloc((void**)&ctx->bkd, bkd_words * 8)) != hipSuccess) return fail(e, "bootstrapping key");
-    if ((e = hipMalloc((void**)&ctx->bkq, bkd_words * 8)) != hipSuccess) return fail(e, "bootstrapping key");
-    if ((e = hipMalloc((void**)&ctx->twfq, 2048 * 4)) != hipSuccess) return fail(e, "twiddles");
-    if ((e = hipMalloc((void**)&ctx->twiq, 2048 * 4)) != hipSuccess) return fail(e, "twiddles");
+    if ((e = hipMalloc((void**)&ctx->bkw, n * dev::kKeyStep * sizeof(dev::fft::cd))) != hipSuccess)
+        return fail(e, "bootstrapping key");
+    if ((e = hipMalloc((void**)&ctx->bkc, n * dev::kKeyStep * sizeof(dev::fft::cd))) != hipSuccess)
+        return fail(e, "bootstrapping key");
+    if ((e = hipMalloc((void**)&ctx->roots, roots.size() * sizeof(dev::fft::cd))) != hipSuccess)
+        return fail(e, "twiddles");
     if ((e = hipMalloc((void**)&ctx->ksk, ksk_dev.size() * 4)) != hipSuccess) return fail(e, "key-switching key");
     if ((e = hipMalloc((void**)&ctx->zero_row, kKskRowWords * 4)) != hipSuccess) return fail(e, "zero row");
     if ((e = hipMalloc((void**)&bk_tmp, bk_words * 4)) != hipSuccess) return fail(e, "bootstrapping key staging");
     if ((e = hipMemcpy(ctx->twf, twf.data(), 1024 * 8, hipMemcpyHostToDevice)) != hipSuccess) return fail(e, "upload");
     if ((e = hipMemcpy(ctx->twi, twi.data(), 1024 * 8, hipMemcpyHostToDevice)) != hipSuccess) return fail(e, "upload");
-    if ((e = hipMemcpy(ctx->twfq, twfq.data(), 2048 * 4, hipMemcpyHostToDevice)) != hipSuccess) return fail(e, "upload");
-    if ((e = hipMemcpy(ctx->twiq, twiq.data(), 2048 * 4, hipMemcpyHostToDevice)) != hipSuccess) return fail(e, "upload");
+    if ((e = hipMemcpy(ctx->roots, roots.data(), roots.size() * sizeof(dev::fft::cd), hipMemcpyHostToDevice)) !=
+        hipSuccess)
+        return fail(e, "upload");
     if ((e = hipMemcpy(ctx->ksk, ksk_dev.data(), ksk_dev.size() * 4, hipMemcpyHostToDevice)) != hipSuccess)
         return fail(e, "upload");
     if ((e = hipMemset(ctx->zero_row, 0, kKskRowWords * 4)) != hipSuccess) return fail(e, "upload");
@@ -270,7 +275,7 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
         return fail(e, "upload");
     if ((e = dev::launch_bk_prepare(bk_tmp, ctx->bkd, ctx->twf, (uint32_t)n, ctx->stream)) != hipSuccess)
         return fail(e, "bootstrapping key transform");
-    if ((e = dev::launch_bk_prepare_q(bk_tmp, ctx->bkq, (const uint64_t*)ctx->twfq, (uint32_t)n, ctx->stream)) !=
+    if ((e = dev::launch_bk_prepare_fft(bk_tmp, ctx->bkw, ctx->bkc, ctx->roots, (uint32_t)n, ctx->stream)) !=
         hipSuccess)
         return fail(e, "bootstrapping key transform");
     if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return fail(e, "bootstrapping key transform");
@@ -282,9 +287,9 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
     ctx->keys.zero_row = ctx->zero_row;
     ctx->keys.twf = ctx->twf;
     ctx->keys.twi = ctx->twi;
-    ctx->keys.bkq = ctx->bkq;
-    ctx->keys.twfq = (const uint64_t*)ctx->twfq;
-    ctx->keys.twiq = (const uint64_t*)ctx->twiq;
+    ctx->keys.bkw = ctx->bkw;
+    ctx->keys.bkc = ctx->bkc;
+    ctx->keys.roots = ctx->roots;
     *out = ctx;
     return FHE_OK;
 }
@@ -299,7 +304,7 @@ extern "C" void fhe_ctx_destroy(fhe_ctx* ctx) {
             for (hipEvent_t ev : tl.ev) ctx->event_pool.push_back(ev);
         for (hipEvent_t ev : ctx->event_pool) (void)hipEventDestroy(ev);
         for (void* p : {(void*)ctx->bkd, (void*)ctx->ksk, (void*)ctx->zero_row, (void*)ctx->twf,
-                        (void*)ctx->twi, (void*)ctx->big, (void*)ctx->bkq, (void*)ctx->twfq, (void*)ctx->twiq})
+                        (void*)ctx->twi, (void*)ctx->big, (void*)ctx->bkw, (void*)ctx->bkc, (void*)ctx->roots})
             if (p) (void)hipFree(p);
         if (ctx->stream) (void)hipStreamDestroy(ctx->stream);
         if (ctx->order) (void)hipEventDestroy(ctx->order);
@@ -435,47 +440,42 @@ extern "C" int fhe_debug_cmux(int device, int arith, const uint32_t* bk_i, int32
     if (rc) return rc;
     DeviceGuard guard(device);
     std::vector<uint64_t> twf, twi;
-    if (arith == 0) {
-        make_twiddles(twf, twi);
-    } else {
-        std::vector<int32_t> f, g;
-        make_twiddles_q(f, g);
-        twf.assign(1024, 0);
-        twi.assign(1024, 0);
-        std::memcpy(twf.data(), f.data(), 8192);
-        std::memcpy(twi.data(), g.data(), 8192);
-    }
+    make_twiddles(twf, twi);
+    std::vector<dev::fft::cd> roots;
+    make_roots(roots);
     uint64_t *d_twf = nullptr, *d_twi = nullptr, *d_bkd = nullptr;
     uint32_t *d_bk = nullptr, *d_acc = nullptr;
+    dev::fft::cd *d_roots = nullptr, *d_bkw = nullptr;
     const size_t bk_words = 4 * 2 * kN, bkd_words = 2 * 32 * 2 * 64;
+    const size_t roots_bytes = roots.size() * sizeof(dev::fft::cd), bkw_bytes = dev::kKeyStep * sizeof(dev::fft::cd);
     hipError_t e = hipSuccess;
     auto step = [&](hipError_t r) { if (e == hipSuccess) e = r; };
     step(hipMalloc((void**)&d_twf, 8192));
     step(hipMalloc((void**)&d_twi, 8192));
     step(hipMalloc((void**)&d_bkd, bkd_words * 8));
+    step(hipMalloc((void**)&d_roots, roots_bytes));
+    step(hipMalloc((void**)&d_bkw, bkw_bytes));
     step(hipMalloc((void**)&d_bk, bk_words * 4));
     step(hipMalloc((void**)&d_acc, 2 * kN * 4));
     if (e == hipSuccess) {
         step(hipMemcpy(d_twf, twf.data(), 8192, hipMemcpyHostToDevice));
         step(hipMemcpy(d_twi, twi.data(), 8192, hipMemcpyHostToDevice));
+        step(hipMemcpy(d_roots, roots.data(), roots_bytes, hipMemcpyHostToDevice));
         step(hipMemcpy(d_bk, bk_i, bk_words * 4, hipMemcpyHostToDevice));
         step(hipMemcpy(d_acc, acc, 2 * kN * 4, hipMemcpyHostToDevice));
     }
     if (e == hipSuccess)
         step(arith == 0 ? dev::launch_bk_prepare(d_bk, d_bkd, d_twf, 1, nullptr)
-                        : dev::launch_bk_prepare_q(d_bk, d_bkd, d_twf, 1, nullptr));
+                        : dev::launch_bk_prepare_fft(d_bk, d_bkw, nullptr, d_roots, 1, nullptr));
     dev::DeviceKeys K{};
-    if (arith == 0) {
-        K.twf = d_twf;
-        K.twi = d_twi;
-    } else {
-        K.twfq = d_twf;
-        K.twiq = d_twi;
-    }
+    K.twf = d_twf;
+    K.twi = d_twi;
+    K.bkw = d_bkw;
+    K.roots = d_roots;
     if (e == hipSuccess) step(dev::launch_debug_cmux(K, arith, d_bkd, abar, d_acc, nullptr));
     if (e == hipSuccess) step(hipDeviceSynchronize());
     if (e == hipSuccess) step(hipMemcpy(acc, d_acc, 2 * kN * 4, hipMemcpyDeviceToHost));
-    for (void* p : {(void*)d_twf, (void*)d_twi, (void*)d_bkd, (void*)d_bk, (void*)d_acc})
+    for (void* p : {(void*)d_twf, (void*)d_twi, (void*)d_bkd, (void*)d_roots, (void*)d_bkw, (void*)d_bk, (void*)d_acc})
         if (p) (void)hipFree(p);
     return e == hipSuccess ? FHE_OK : hip_fail(e, "fhe_debug_cmux");
 }

@@ -19,8 +19,10 @@ namespace fhe {
 
 namespace {
 
+// What the tuner times: arithmetic 1 with one wave per gate runs groups of
+// four gates whatever gates_per_group says, so only one of those is listed.
 constexpr dev::LaunchConfig kShapes[] = {{1, 1, 0}, {1, 2, 0}, {1, 4, 0}, {1, 8, 0}, {2, 1, 0},
-                                         {1, 1, 1}, {1, 2, 1}, {1, 4, 1}, {1, 8, 1}, {2, 1, 1}, {4, 1, 1}};
+                                         {1, 4, 1}, {2, 1, 1}, {4, 1, 1}};
 
 bool same(const dev::LaunchConfig& a, const dev::LaunchConfig& b) {
     return a.waves_per_gate == b.waves_per_gate && a.gates_per_group == b.gates_per_group && a.arith == b.arith;
@@ -42,17 +44,15 @@ int tune_bucket(size_t width) {
     return b;
 }
 
-// Before any measurement (defaults from measurements on MI355X): two-prime
-// arithmetic everywhere; four waves per gate up to one gate per CU, two
-// waves per gate up to two; one wave per SIMD with the full register file
-// (four gates per workgroup, one 81 KB workgroup per CU) up to four gates
-// per CU; eight gates per workgroup (two waves per SIMD) beyond.
+// Before any measurement: FFT arithmetic everywhere; four waves per gate up to
+// one gate per CU, two waves per gate up to two, groups of four gates beyond.
+// Measured blind rotations (ms) at 256 / 512 / 1,024 gates on 256 CUs: four
+// waves 2.2 / 4.4 / 8.8, two waves 2.7 / 3.0 / 6.0, groups 4.8 / 4.8 / 4.8.
 static dev::LaunchConfig default_shape(const fhe_ctx* ctx, size_t width) {
     const size_t cus = (size_t)ctx->cu_count;
     if (width <= cus) return dev::LaunchConfig{4, 1, 1};
     if (width <= 2 * cus) return dev::LaunchConfig{2, 1, 1};
-    if (width <= 4 * cus) return dev::LaunchConfig{1, 4, 1};
-    return dev::LaunchConfig{1, 8, 1};
+    return dev::LaunchConfig{1, 4, 1};
 }
 
 void tune_defaults(fhe_ctx* ctx) {
