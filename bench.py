@@ -44,14 +44,12 @@ LANE_OPS_PER_GATE = {
 # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one 32-bit integer op or one f64
 # fused multiply-add (78.6 TFLOP/s) per lane-cycle.
 VALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
-# Key switching gathers rows of the key-switching key: per gate 1,024 input
-# coefficients x 8 base-4 digits, three quarters of them non-zero on average,
-# each selecting one 501-word row (2,004 B).  The 50 MB key is far larger
-# than one XCD's 4 MB L2 but rows are shared by the gates of a launch, so the
-# gathers are served mostly from L2: the roof is the aggregate L2 bandwidth,
-# 8 XCDs x 16 channels x 128 B per clock x 2.4 GHz.
-KS_BYTES_PER_GATE = 1024 * 8 * 3 // 4 * 501 * 4
-L2_PEAK_TBS = 8 * 16 * 128 * 2.4e9 / 1e12
+# Key switching is an int8 matrix product: per gate 1,024 input coefficients x
+# 8 base-4 digits x 3 non-zero digit values against 501 words of four byte
+# limbs, two operations each, against the dense int8 rate of 256 CUs x 8,192
+# operations per clock x 2.4 GHz.
+KS_OPS_PER_GATE = 1024 * 8 * 3 * 501 * 4 * 2
+I8_PEAK_TOPS = 256 * 8192 * 2.4e9 / 1e12
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "blind_rotate_traffic.json")
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2005_01945_amd", "csrc", f)
                for f in ("kernels.hip", "fft.h", "goldilocks.h")]
@@ -340,15 +338,14 @@ def roofline_of(records):
 
 
 def key_switch_roof(records):
-    """Key switching against the aggregate L2 bandwidth: algorithmic bytes =
-    the expected 6,144 non-zero digit rows of 2,004 B gathered per gate."""
+    """Key switching against the dense int8 matrix rate."""
     gates = sum(r["gates"] for r in records)
     ms = sum(r["key_switch_ms"] for r in records)
     if not gates or ms <= 0:
         return None
-    achieved = KS_BYTES_PER_GATE * gates / (ms / 1e3) / 1e12
-    return {"bound": "l2", "achieved": round(achieved, 3), "peak": round(L2_PEAK_TBS, 2), "unit": "TB/s",
-            "frac": round(achieved / L2_PEAK_TBS, 4), "ms": round(ms, 3), "gates": gates}
+    achieved = KS_OPS_PER_GATE * gates / (ms / 1e3) / 1e12
+    return {"bound": "mfma_i8", "achieved": round(achieved, 3), "peak": round(I8_PEAK_TOPS, 2), "unit": "TOP/s",
+            "frac": round(achieved / I8_PEAK_TOPS, 4), "ms": round(ms, 3), "gates": gates}
 
 
 def time_config(F, ctx, cfg, steps, warmup):

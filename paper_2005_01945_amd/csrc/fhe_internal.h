@@ -20,7 +20,10 @@ constexpr uint32_t kKsT = 8;         // key-switch digits
 constexpr uint32_t kKsBaseBit = 2;
 constexpr uint32_t kKsBase = 1u << kKsBaseBit;
 constexpr uint32_t kMu = 1u << 29;   // 1/8 on the torus
-constexpr uint32_t kKskRowWords = 512;  // one KS row padded to 2 KB for 16-byte loads
+// One extracted sample in scratch: 512 words of two kept 16-bit values each,
+// the body, and padding to a multiple of 16 bytes.
+constexpr uint32_t kSampleWords = kN / 2 + 4;
+constexpr size_t kKsbBytes = (size_t)64 * 256 * 3 * 1024;  // byte limbs of the KS rows, 501 words padded to 512
 
 // Sets the thread-local error message and returns `code`.
 int set_error(int code, const char* fmt, ...);

@@ -51,8 +51,7 @@ struct GateIO {
 // Per-context device key material.
 struct DeviceKeys {
     const uint64_t* bkd;      // BK in the NTT domain, kernel layout (32 MB)
-    const uint32_t* ksk;      // KSK rows v = 1..3, [N][t][3][512] (50 MB)
-    const uint32_t* zero_row; // 512 zero words (digit 0 rows)
+    const uint8_t* ksb;       // KSK rows v = 1..3 as byte limbs in matrix-operand order (50 MB)
     const uint64_t* twf;      // forward twiddles [32][32]
     const uint64_t* twi;      // inverse twiddles (with N^-1) [32][32]
     // FFT products: BK halves at the leaves in the two kernels' layouts (65.5
@@ -87,8 +86,12 @@ struct LaunchConfig {
     uint32_t arith;
 };
 
-// Gate prologue + blind rotation + sample extraction: writes big[g][N+1]
-// (big[2g], big[2g+1] with pair_slots).
+// KSK (uint32 [N][t][4][n + 1], device) -> rows v = 1..3 in the operand order
+// of key switching.
+hipError_t launch_ksk_prepare(const uint32_t* ksk, uint8_t* ksb, hipStream_t s);
+
+// Gate prologue + blind rotation + sample extraction: writes big[g]
+// [kSampleWords] (big[2g], big[2g+1] with pair_slots).
 hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* big,
                                uint32_t count, LaunchConfig cfg, hipStream_t s);
 

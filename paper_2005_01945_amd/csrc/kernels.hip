@@ -765,12 +765,21 @@ __device__ __forceinline__ void acc_init(uint32_t (&acc)[2][1024], int bbar, int
     }
 }
 
+// An extracted sample as key switching reads it: word q of 512 holds the 16
+// bits kept of a'_2q (low half) and a'_(2q+1), i.e. eight base-4 digits each;
+// word 512 is b'.  Slots are kSampleWords apart.
+__device__ __forceinline__ uint32_t kept_bits(uint32_t a) { return (a + (1u << 15)) >> 16; }
+__device__ __forceinline__ uint32_t pack_kept(uint32_t even, uint32_t odd) {
+    return kept_bits(even) | kept_bits(odd) << 16;
+}
+
 // Sample extraction of coefficient 0: a'_0 = a_0, a'_m = -a_(N-m), b' = b_0,
 // by THREADS threads with index `tid`.
 template <int THREADS>
 __device__ __forceinline__ void sample_extract(const uint32_t (&acc)[2][1024], uint32_t* o, int tid) {
-    for (int m = tid; m < N; m += THREADS) o[m == 0 ? 0 : N - m] = m == 0 ? acc[0][0] : 0u - acc[0][m];
-    if (tid == 0) o[N] = acc[1][0];
+    for (int q = tid; q < N / 2; q += THREADS)
+        o[q] = pack_kept(q == 0 ? acc[0][0] : 0u - acc[0][N - 2 * q], 0u - acc[0][N - 2 * q - 1]);
+    if (tid == 0) o[N / 2] = acc[1][0];
 }
 
 // Compound gate outputs.  The accumulator was rotated from the test vector
@@ -788,16 +797,23 @@ __device__ __forceinline__ void compound_extract(const uint32_t (&acc)[2][1024],
     const int32_t b0 = sym_value(op1, 0), b1 = sym_value(op1, 1), b2 = sym_value(op1, 2);
     const uint32_t x0 = (uint32_t)(a1 - a2), y0 = (uint32_t)(a1 - a0);
     const uint32_t x1 = (uint32_t)(b1 - b2), y1 = (uint32_t)(b1 - b0);
-    for (int j = tid; j < N; j += THREADS) {
-        const uint32_t e1 = j <= m1 ? acc[0][m1 - j] : 0u - acc[0][N + m1 - j];
-        const uint32_t e2 = j <= m2 ? acc[0][m2 - j] : 0u - acc[0][N + m2 - j];
-        o0[j] = x0 * e1 + y0 * e2;
-        o1[j] = x1 * e1 + y1 * e2;
+    for (int q = tid; q < N / 2; q += THREADS) {
+        uint32_t v0[2], v1[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int j = 2 * q + s;
+            const uint32_t e1 = j <= m1 ? acc[0][m1 - j] : 0u - acc[0][N + m1 - j];
+            const uint32_t e2 = j <= m2 ? acc[0][m2 - j] : 0u - acc[0][N + m2 - j];
+            v0[s] = x0 * e1 + y0 * e2;
+            v1[s] = x1 * e1 + y1 * e2;
+        }
+        o0[q] = pack_kept(v0[0], v0[1]);
+        o1[q] = pack_kept(v1[0], v1[1]);
     }
     if (tid == 0) {
         const uint32_t e1 = acc[1][m1], e2 = acc[1][m2];
-        o0[N] = x0 * e1 + y0 * e2 + (uint32_t)(a0 + a2) * (kMu >> 1);
-        o1[N] = x1 * e1 + y1 * e2 + (uint32_t)(b0 + b2) * (kMu >> 1);
+        o0[N / 2] = x0 * e1 + y0 * e2 + (uint32_t)(a0 + a2) * (kMu >> 1);
+        o1[N / 2] = x1 * e1 + y1 * e2 + (uint32_t)(b0 + b2) * (kMu >> 1);
     }
 }
 
@@ -808,16 +824,16 @@ template <int THREADS>
 __device__ __forceinline__ void gate_epilogue(const GateIO& io, uint32_t g, const uint32_t (&acc)[2][1024],
                                               uint32_t* __restrict__ big, int tid) {
     const GateMode m = gate_mode(io, g);
-    uint32_t* o = big + (size_t)(io.pair_slots ? 2 * g : g) * (N + 1);
+    uint32_t* o = big + (size_t)(io.pair_slots ? 2 * g : g) * kSampleWords;
     if (!m.valid) {
-        const int words = (io.pair_slots ? 2 : 1) * (N + 1);
+        const int words = (io.pair_slots ? 2 : 1) * kSampleWords;
         for (int j = tid; j < words; j += THREADS) o[j] = 0u;
         if (tid == 0 && io.err)
             __hip_atomic_store(io.err, 0x100u | (m.op0 & 0xFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         return;
     }
     if (m.compound)
-        compound_extract<THREADS>(acc, m.op0, m.op1, o, o + N + 1, tid);
+        compound_extract<THREADS>(acc, m.op0, m.op1, o, o + kSampleWords, tid);
     else
         sample_extract<THREADS>(acc, o, tid);
 }
@@ -1210,109 +1226,146 @@ void k_debug_cmux_fft(DeviceKeys K, int32_t abar, uint32_t* __restrict__ accg) {
 }
 
 // Key switching N -> n: out = (0, b') - sum_{i,j} KSK[i][j][d_ij], d_ij the
-// j-th base-4 digit of a'_i rounded to 16 bits.  One wave per gate; lane l
-// owns output words 8l .. 8l+7 and gathers 2 KB rows with 16-byte loads; a
-// zero digit (a quarter of them) skips its row.
-__global__ __launch_bounds__(kBlockThreads) void k_key_switch(DeviceKeys K, GateIO io,
-                                                              const uint32_t* __restrict__ big,
-                                                              uint32_t count) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t g = blockIdx.x * kWavesPerBlock + wave;
-    if (g >= count) return;
-    uint32_t* o = ks_output(io, g);
-    if (!o) return;  // unused second slot of a single gate
-    const uint32_t* src = big + (size_t)g * (N + 1);
-    uint32_t acc[8];
+// j-th base-4 digit of the 16 bits kept of a'_i.
+//
+// As a matrix product on the int8 matrix cores: a gate's row of A holds, for
+// each of the 8,192 digits and each value v = 1, 2, 3, the byte [d == v]; B
+// holds the key-switching rows as four signed byte limbs per word
+// (w = s0 + 2^8 s1 + 2^16 s2 + 2^24 s3 mod 2^32).  Each limb's sum is at most
+// 8,192 * 128 = 2^20 in magnitude, exact in the 32-bit accumulators, and the
+// limbs recombine modulo 2^32: the words are those of the row sums.  The
+// product does four times the additions of the gathers it replaces, on units
+// with 128 times the rate, and reads every key row once per 32 or 64 gates
+// instead of once per use.
+//
+// One instruction multiplies 32 gates x 32 digits of one value v x 8 words (32
+// limb columns, column 4 word + limb).  Its k order is lane half h, byte t:
+// digit field at bit 8 (t / 4) + 2 (t % 4) of sample word 256 h + kc, so that a
+// lane builds its A operand from one sample word: the flags of a value are
+// bits 0, 2, 4, 6 of each byte, which a 24-bit product with 1 + 2^6 + 2^12 +
+// 2^18 spreads to the low bits of four bytes.  B is stored in operand order.
+// A workgroup takes MT x 32 gates and NF x 8 words and splits the 256 steps kc
+// over KW waves, whose sums meet in LDS.
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+template <int MT, int NF, int KW>
+__global__ __launch_bounds__(64 * KW) void k_key_switch(DeviceKeys K, GateIO io, const uint32_t* __restrict__ big,
+                                                        uint32_t count) {
+    __shared__ uint32_t red[32 * MT][8 * NF];
+    constexpr int kThreads = 64 * KW, kGates = 32 * MT, kSteps = 256 / KW;
+    const int lane = threadIdx.x & 63, kw = threadIdx.x >> 6, h = lane >> 5;
+    const uint32_t gate0 = blockIdx.x / (64 / NF) * kGates, frag0 = blockIdx.x % (64 / NF) * NF;
+    for (int k = threadIdx.x; k < kGates * 8 * NF; k += kThreads) (&red[0][0])[k] = 0u;
+    __syncthreads();
+
+    const uint32_t* arow[MT];  // this lane's half of its gates' sample words
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = (8 * lane + e == NLWE) ? src[N] : 0u;
-#pragma unroll 1
-    for (int i0 = 0; i0 < N; i0 += 64) {
-        const uint32_t digits = (src[i0 + lane] + (1u << 15)) >> 16;
-#pragma unroll 1
-        for (int l = 0; l < 64; ++l) {
-            const uint32_t dd = __builtin_amdgcn_readlane(digits, l);
-            const size_t rowbase = ((size_t)(i0 + l) * kKsT) * 3;
-#pragma unroll
-            for (int j = 0; j < (int)kKsT; ++j) {
-                const uint32_t d = (dd >> (14 - 2 * j)) & 3u;
-                if (d == 0) continue;  // uniform over the wave: a zero digit selects no row
-                const uint4* row = reinterpret_cast<const uint4*>(K.ksk + (rowbase + 3 * j + d - 1) * kKskRowWords);
-                const uint4 v0 = row[2 * lane], v1 = row[2 * lane + 1];
-                acc[0] -= v0.x; acc[1] -= v0.y; acc[2] -= v0.z; acc[3] -= v0.w;
-                acc[4] -= v1.x; acc[5] -= v1.y; acc[6] -= v1.z; acc[7] -= v1.w;
-            }
-        }
+    for (int m = 0; m < MT; ++m) {
+        const uint32_t g = gate0 + 32 * m + (lane & 31);
+        arow[m] = big + (size_t)(g < count ? g : count - 1) * kSampleWords + 256 * h + kSteps * kw;
     }
+    const v4i* bp = reinterpret_cast<const v4i*>(K.ksb) + ((size_t)frag0 * 256 + kSteps * kw) * 3 * 64 + lane;
+    v16i acc[MT][NF];
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-        if (8 * lane + e < NW) o[8 * lane + e] = acc[e];
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[m][f][r] = 0;
+    v4i bn[3][NF];
+    auto load_b = [&](int kc) {
+#pragma unroll
+        for (int v = 0; v < 3; ++v)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) bn[v][f] = bp[((size_t)f * 256 + kc) * 192 + v * 64];
+    };
+    load_b(0);
+#pragma unroll 1
+    for (int kc = 0; kc < kSteps; kc += 4) {
+        uint4 aw[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) aw[m] = *reinterpret_cast<const uint4*>(arow[m] + kc);
+        static_for<0, 4>([&](auto U) {
+            constexpr int u = decltype(U)::value;
+            v4i b[3][NF];
+#pragma unroll
+            for (int v = 0; v < 3; ++v)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) b[v][f] = bn[v][f];
+            load_b(kc + u + 1 < kSteps ? kc + u + 1 : kc + u);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const uint32_t w = u == 0 ? aw[m].x : u == 1 ? aw[m].y : u == 2 ? aw[m].z : aw[m].w;
+                const uint32_t lo = w & 0x55555555u, hi = (w >> 1) & 0x55555555u;
+                const uint32_t both = lo & hi;
+                const uint32_t flags[3] = {lo ^ both, hi ^ both, both};
+#pragma unroll
+                for (int v = 0; v < 3; ++v) {
+                    v4i a;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        a[c] = (int)(__umul24((flags[v] >> (8 * c)) & 0xFFu, 0x41041u) & 0x01010101u);
+#pragma unroll
+                    for (int f = 0; f < NF; ++f)
+                        acc[m][f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b[v][f], acc[m][f], 0, 0, 0);
+                }
+            }
+        });
+    }
+
+    // limbs of a word are in four neighbouring lanes: shift, add over the
+    // quad, and lane `limb` adds the rows r with r % 4 == limb to LDS
+    const int limb = lane & 3, word = (lane >> 2) & 7;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                uint32_t v = 0;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    uint32_t x = (uint32_t)acc[m][f][4 * a + r] << (8 * limb);
+                    x += (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
+                    x += (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
+                    v = limb == r ? x : v;
+                }
+                lds_add(&red[32 * m + 8 * a + 4 * h + limb][8 * f + word], v);
+            }
+    __syncthreads();
+    for (int k = threadIdx.x; k < kGates * 8 * NF; k += kThreads) {
+        const uint32_t g = gate0 + k / (8 * NF), w = 8 * frag0 + k % (8 * NF);
+        if (g >= count || w >= NW) continue;
+        uint32_t* o = ks_output(io, g);
+        if (!o) continue;  // unused second slot of a single gate
+        o[w] = (w == NLWE ? big[(size_t)g * kSampleWords + N / 2] : 0u) - (&red[0][0])[k];
+    }
 }
 
-// Key switching with W waves per gate: wave w sums the rows of coefficients
-// (N/W) w .. (N/W)(w + 1) - 1, the W partial sums meet in LDS and wave 0
-// writes the result.  SKIP: zero digits (a quarter of them) skip their row
-// by a branch uniform over the wave, at the price of serialising the row
-// loads of a coefficient; otherwise they read the all-zero row.  Per launch
-// width the fastest form was measured (ms per launch; "1" is k_key_switch,
-// which skips):
-//   gates    8 waves   4+skip   2+skip   1
-//   256      0.15      0.35     0.60
-//   1,024    0.56      0.46     0.68     1.05
-//   1,536    0.82      0.62     0.74
-//   2,048    1.07      1.71     0.82     1.13
-//   2,560    1.29      2.31     1.09     1.29
-//   6,144    3.20                        2.26
-//   8,192    4.27                        6.05
-//   16,384   8.52      22.3     20.6     17.3 (without skip)
-// With eight waves a skip costs 8.5 -> 21.3 ms at 16,384 gates, and staging
-// the rows of a coefficient in LDS once per workgroup of eight gates 12.4 ms.
-constexpr uint32_t kKsSplit4Min = 769, kKsSplit2Min = 1793, kKsOneWaveMin = 2817, kKsOneWaveMax = 6144;
-
-template <int W, bool SKIP>
-__global__ __launch_bounds__(64 * W) void k_key_switch_split(DeviceKeys K, GateIO io,
-                                                             const uint32_t* __restrict__ big, uint32_t count) {
-    __shared__ uint32_t part[W][512];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t g = blockIdx.x;
-    if (g >= count) return;  // uniform over the block
-    uint32_t* o = ks_output(io, g);
-    if (!o) return;  // unused second slot of a single gate (uniform over the block)
-    const uint32_t* src = big + (size_t)g * (N + 1);
-    uint32_t acc[8];
+// KSK [N][t][4][501] -> operand B of k_key_switch, bytes
+// [8-word group][kc][v][lane][t]: lane = 32 h + 4 word + limb, digit field at
+// bit p = 8 (t / 4) + 2 (t % 4) of sample word 256 h + kc.
+__global__ __launch_bounds__(256) void k_ksk_prepare(const uint32_t* __restrict__ ksk, uint8_t* __restrict__ ksb) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t block = blockIdx.x * 4 + (threadIdx.x >> 6);  // [group][kc][v]
+    const uint32_t v = block % 3, kc = block / 3 % 256, group = block / 768;
+    const uint32_t w = 8 * group + ((lane >> 2) & 7), limb = lane & 3, q = 256 * (lane >> 5) + kc;
+    uint32_t out[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = (wave == 0 && 8 * lane + e == NLWE) ? src[N] : 0u;
-    const uint4* zero = reinterpret_cast<const uint4*>(K.zero_row);
-    constexpr int kPerWave = N / W;
-#pragma unroll 1
-    for (int i0 = wave * kPerWave; i0 < (wave + 1) * kPerWave; i0 += 64) {
-        const uint32_t digits = (src[i0 + lane] + (1u << 15)) >> 16;
-#pragma unroll 1
-        for (int l = 0; l < 64; ++l) {
-            const uint32_t dd = __builtin_amdgcn_readlane(digits, l);
-            const size_t rowbase = ((size_t)(i0 + l) * kKsT) * 3;
+    for (int c = 0; c < 4; ++c) {
+        uint32_t packed = 0;
 #pragma unroll
-            for (int j = 0; j < (int)kKsT; ++j) {
-                const uint32_t d = (dd >> (14 - 2 * j)) & 3u;
-                if (SKIP && d == 0) continue;
-                const uint4* row = d ? reinterpret_cast<const uint4*>(K.ksk + (rowbase + 3 * j + d - 1) * kKskRowWords)
-                                     : zero;
-                const uint4 v0 = row[2 * lane], v1 = row[2 * lane + 1];
-                acc[0] -= v0.x; acc[1] -= v0.y; acc[2] -= v0.z; acc[3] -= v0.w;
-                acc[4] -= v1.x; acc[5] -= v1.y; acc[6] -= v1.z; acc[7] -= v1.w;
-            }
+        for (int b = 0; b < 4; ++b) {
+            const uint32_t p = 8 * c + 2 * b;
+            const uint32_t i = 2 * q + (p >> 4), j = 7 - (p & 15) / 2;
+            uint32_t x = w < NW ? ksk[((size_t)(i * kKsT + j) * kKsBase + v + 1) * NW + w] : 0u;
+            for (uint32_t l = 0; l < limb; ++l) x = (x - (uint32_t)(int32_t)(int8_t)x) >> 8;
+            packed |= (x & 0xFFu) << (8 * b);
         }
+        out[c] = packed;
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) part[wave][8 * lane + e] = acc[e];
-    __syncthreads();
-    if (wave != 0) return;
-#pragma unroll
-    for (int w = 1; w < W; ++w)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += part[w][8 * lane + e];
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        if (8 * lane + e < NW) o[8 * lane + e] = acc[e];
+    reinterpret_cast<uint4*>(ksb)[(size_t)block * 64 + lane] = make_uint4(out[0], out[1], out[2], out[3]);
 }
 
 // BK (uint32 [n][4][2][N]) -> NTT domain in the layout cmux_step reads:
@@ -1449,19 +1502,38 @@ hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* 
     }
 }
 
+template <int MT, int NF, int KW>
+static hipError_t launch_key_switch_shape(const DeviceKeys& K, const GateIO& io, const uint32_t* big, uint32_t count,
+                                          hipStream_t s) {
+    constexpr uint32_t gates = 32 * MT;
+    hipLaunchKernelGGL((k_key_switch<MT, NF, KW>), dim3(64 / NF * ((count + gates - 1) / gates)), dim3(64 * KW), 0, s,
+                       K, io, big, count);
+    return hipGetLastError();
+}
+
 hipError_t launch_key_switch(const DeviceKeys& K, const GateIO& io, const uint32_t* big,
                              uint32_t count, hipStream_t s) {
     if (count == 0) return hipSuccess;
-    if (count >= kKsOneWaveMin && count <= kKsOneWaveMax) {
-        const uint32_t blocks = (count + kWavesPerBlock - 1) / kWavesPerBlock;
-        hipLaunchKernelGGL(k_key_switch, dim3(blocks), dim3(kBlockThreads), 0, s, K, io, big, count);
-    } else if (count >= kKsSplit2Min && count < kKsOneWaveMin) {
-        hipLaunchKernelGGL((k_key_switch_split<2, true>), dim3(count), dim3(128), 0, s, K, io, big, count);
-    } else if (count >= kKsSplit4Min && count < kKsSplit2Min) {
-        hipLaunchKernelGGL((k_key_switch_split<4, true>), dim3(count), dim3(256), 0, s, K, io, big, count);
-    } else {
-        hipLaunchKernelGGL((k_key_switch_split<8, false>), dim3(count), dim3(512), 0, s, K, io, big, count);
-    }
+    // Few gates: every workgroup streams its columns of B once, so more and
+    // narrower column groups (and fewer gates per instruction) fill more
+    // compute units.  Many gates: more columns per workgroup share the A
+    // operands, which cost 41 VALU per 3 x 4 operand words.  us per launch at
+    // 128 / 256 / 512 / 1,024 / 16,384 gates (the row gathers this replaces:
+    // 145 / 145 / 280 / 440 / 8,500):
+    //   <1, 1, 16>  18 / 31 / 56 / 106 / 1,609
+    //   <2, 1, 16>  23 / 24 / 43 /  80 / 1,187
+    //   <2, 2, 16>  30 / 30 / 34 /  65 /   918
+    //   <2, 4,  8>  49 / 47 / 48 /  56 /   808   (0.41 of the int8 rate)
+    // Four waves on four gate groups that share B through L1 instead of the
+    // split over steps: 998 at 16,384.
+    if (count <= 128) return launch_key_switch_shape<1, 1, 16>(K, io, big, count, s);
+    if (count <= 256) return launch_key_switch_shape<2, 1, 16>(K, io, big, count, s);
+    if (count <= 512) return launch_key_switch_shape<2, 2, 16>(K, io, big, count, s);
+    return launch_key_switch_shape<2, 4, 8>(K, io, big, count, s);
+}
+
+hipError_t launch_ksk_prepare(const uint32_t* ksk, uint8_t* ksb, hipStream_t s) {
+    hipLaunchKernelGGL(k_ksk_prepare, dim3(64 * 256 * 3 / 4), dim3(256), 0, s, ksk, ksb);
     return hipGetLastError();
 }
 

@@ -3,7 +3,7 @@
 // harnesses that forbid allocation).
 //
 // The batched gate call needs scratch memory for the extracted N-dimensional
-// samples between the blind rotation and the key switching (N + 1 words per
+// samples between the blind rotation and the key switching (kSampleWords per
 // gate).  Here that scratch is a fixed device array of this translation unit,
 // one copy per GPU, resolved to its device address once per device.
 #include <hip/hip_runtime.h>
@@ -18,10 +18,10 @@ namespace fhe {
 
 constexpr size_t kNoAllocMaxGates = 4096;
 
-// Extracted samples of up to kNoAllocMaxGates gates (16.8 MB per GPU).  In
+// Extracted samples of up to kNoAllocMaxGates gates (8.5 MB per GPU).  In
 // host code this name is not a device address: only the pointer resolved by
 // hipGetSymbolAddress below is passed to kernels.
-static __device__ __align__(256) uint32_t scratch[kNoAllocMaxGates * (kN + 1)];
+static __device__ __align__(256) uint32_t scratch[kNoAllocMaxGates * kSampleWords];
 
 namespace {
 constexpr int kMaxDevices = 64;

@@ -2,8 +2,8 @@
 //
 // A context keeps the cloud key resident on one GPU: the bootstrapping key
 // converted once to the FFT domain (two layouts of 65.5 MB) and to the NTT
-// domain (32.8 MB), the key-switching key laid out as 2 KB rows (50.3 MB), and
-// the twiddle tables.  Gate batches run as two
+// domain (32.8 MB), the key-switching key as byte limbs for the int8 matrix
+// cores (50.3 MB), and the twiddle tables.  Gate batches run as two
 // launches on the caller's stream: blind rotation (with the gate prologue and
 // sample extraction fused in) and key switching.
 #include <hip/hip_runtime.h>
@@ -103,7 +103,7 @@ int check_gfx950(int device) {
 }
 
 int ctx_reserve_big(fhe_ctx* ctx, size_t gates) {
-    const size_t need = gates * (kN + 1);
+    const size_t need = gates * kSampleWords;
     if (need <= ctx->big_cap) return FHE_OK;
     if (ctx->big) {
         hipError_t e = hipDeviceSynchronize();  // work in flight may still read the old buffer
@@ -112,7 +112,7 @@ int ctx_reserve_big(fhe_ctx* ctx, size_t gates) {
         ctx->big = nullptr;
         ctx->big_cap = 0;
     }
-    size_t cap = need < (size_t)4096 * (kN + 1) ? (size_t)4096 * (kN + 1) : need;
+    size_t cap = need < (size_t)4096 * kSampleWords ? (size_t)4096 * kSampleWords : need;
     hipError_t e = hipMalloc((void**)&ctx->big, cap * sizeof(uint32_t));
     if (e != hipSuccess) return hip_fail(e, "scratch allocation");
     ctx->big_cap = cap;
@@ -222,20 +222,12 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
     const size_t n = ck->P.n, N = ck->P.N;
     const size_t bk_words = n * 4 * 2 * N;
     const size_t bkd_words = n * 2 * 32 * 2 * 64;
-    const size_t ksk_rows = N * kKsT * 3;
-
-    // KS rows v = 1..3, each padded to 512 words.
-    std::vector<uint32_t> ksk_dev(ksk_rows * kKskRowWords, 0u);
-    for (size_t i = 0; i < N; ++i)
-        for (size_t j = 0; j < kKsT; ++j)
-            for (size_t v = 1; v < kKsBase; ++v)
-                std::memcpy(&ksk_dev[((i * kKsT + j) * 3 + v - 1) * kKskRowWords],
-                            &ck->ksk[((i * kKsT + j) * kKsBase + v) * (n + 1)], (n + 1) * sizeof(uint32_t));
-
     uint32_t* bk_tmp = nullptr;
+    uint32_t* ksk_tmp = nullptr;
     auto fail = [&](hipError_t e, const char* what) {
         int code = hip_fail(e, what);
         if (bk_tmp) (void)hipFree(bk_tmp);
+        if (ksk_tmp) (void)hipFree(ksk_tmp);
         fhe_ctx_destroy(ctx);
         return code;
     };
@@ -260,17 +252,17 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
         return fail(e, "bootstrapping key");
     if ((e = hipMalloc((void**)&ctx->roots, roots.size() * sizeof(dev::fft::cd))) != hipSuccess)
         return fail(e, "twiddles");
-    if ((e = hipMalloc((void**)&ctx->ksk, ksk_dev.size() * 4)) != hipSuccess) return fail(e, "key-switching key");
-    if ((e = hipMalloc((void**)&ctx->zero_row, kKskRowWords * 4)) != hipSuccess) return fail(e, "zero row");
+    if ((e = hipMalloc((void**)&ctx->ksb, kKsbBytes)) != hipSuccess) return fail(e, "key-switching key");
+    if ((e = hipMalloc((void**)&ksk_tmp, ck->ksk.size() * 4)) != hipSuccess)
+        return fail(e, "key-switching key staging");
     if ((e = hipMalloc((void**)&bk_tmp, bk_words * 4)) != hipSuccess) return fail(e, "bootstrapping key staging");
     if ((e = hipMemcpy(ctx->twf, twf.data(), 1024 * 8, hipMemcpyHostToDevice)) != hipSuccess) return fail(e, "upload");
     if ((e = hipMemcpy(ctx->twi, twi.data(), 1024 * 8, hipMemcpyHostToDevice)) != hipSuccess) return fail(e, "upload");
     if ((e = hipMemcpy(ctx->roots, roots.data(), roots.size() * sizeof(dev::fft::cd), hipMemcpyHostToDevice)) !=
         hipSuccess)
         return fail(e, "upload");
-    if ((e = hipMemcpy(ctx->ksk, ksk_dev.data(), ksk_dev.size() * 4, hipMemcpyHostToDevice)) != hipSuccess)
+    if ((e = hipMemcpy(ksk_tmp, ck->ksk.data(), ck->ksk.size() * 4, hipMemcpyHostToDevice)) != hipSuccess)
         return fail(e, "upload");
-    if ((e = hipMemset(ctx->zero_row, 0, kKskRowWords * 4)) != hipSuccess) return fail(e, "upload");
     if ((e = hipMemcpy(bk_tmp, ck->bk.data(), bk_words * 4, hipMemcpyHostToDevice)) != hipSuccess)
         return fail(e, "upload");
     if ((e = dev::launch_bk_prepare(bk_tmp, ctx->bkd, ctx->twf, (uint32_t)n, ctx->stream)) != hipSuccess)
@@ -278,13 +270,16 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
     if ((e = dev::launch_bk_prepare_fft(bk_tmp, ctx->bkw, ctx->bkc, ctx->roots, (uint32_t)n, ctx->stream)) !=
         hipSuccess)
         return fail(e, "bootstrapping key transform");
-    if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return fail(e, "bootstrapping key transform");
+    if ((e = dev::launch_ksk_prepare(ksk_tmp, ctx->ksb, ctx->stream)) != hipSuccess)
+        return fail(e, "key-switching key layout");
+    if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return fail(e, "key preparation");
     (void)hipFree(bk_tmp);
+    (void)hipFree(ksk_tmp);
     bk_tmp = nullptr;
+    ksk_tmp = nullptr;
 
     ctx->keys.bkd = ctx->bkd;
-    ctx->keys.ksk = ctx->ksk;
-    ctx->keys.zero_row = ctx->zero_row;
+    ctx->keys.ksb = ctx->ksb;
     ctx->keys.twf = ctx->twf;
     ctx->keys.twi = ctx->twi;
     ctx->keys.bkw = ctx->bkw;
@@ -303,7 +298,7 @@ extern "C" void fhe_ctx_destroy(fhe_ctx* ctx) {
         for (auto& tl : ctx->timed)
             for (hipEvent_t ev : tl.ev) ctx->event_pool.push_back(ev);
         for (hipEvent_t ev : ctx->event_pool) (void)hipEventDestroy(ev);
-        for (void* p : {(void*)ctx->bkd, (void*)ctx->ksk, (void*)ctx->zero_row, (void*)ctx->twf,
+        for (void* p : {(void*)ctx->bkd, (void*)ctx->ksb, (void*)ctx->twf,
                         (void*)ctx->twi, (void*)ctx->big, (void*)ctx->bkw, (void*)ctx->bkc, (void*)ctx->roots})
             if (p) (void)hipFree(p);
         if (ctx->stream) (void)hipStreamDestroy(ctx->stream);

@@ -21,14 +21,13 @@ struct fhe_ctx {
     fhe_params P{};
     hipStream_t stream = nullptr;  // internal stream (key preparation)
     uint64_t* bkd = nullptr;
-    uint32_t* ksk = nullptr;
-    uint32_t* zero_row = nullptr;
+    uint8_t* ksb = nullptr;
     uint64_t* twf = nullptr;
     uint64_t* twi = nullptr;
     fhe::dev::fft::cd* bkw = nullptr;    // BK for the FFT products, both layouts
     fhe::dev::fft::cd* bkc = nullptr;
     fhe::dev::fft::cd* roots = nullptr;  // exp(i pi k / 1024), k < 2048
-    uint32_t* big = nullptr;  // extracted samples of the gates in flight, [gates][N+1]
+    uint32_t* big = nullptr;  // extracted samples of the gates in flight, [gates][kSampleWords]
     size_t big_cap = 0;       // words
     uint64_t big_generation = 0;  // bumped on every reallocation of big (captured graphs hold it)
     bool use_graphs = true;       // replay circuit level schedules as captured HIP graphs
