@@ -139,6 +139,24 @@ __device__ __forceinline__ void forward_root(cd (&x)[R]) {
     });
 }
 
+// Forward on R registers below a lane's own root, the butterflies of stored
+// twiddle F (see forward_lane) only.
+template <int R, int F>
+__device__ __forceinline__ void forward_lane_part(cd (&x)[R], const cd& t) {
+    constexpr int l = F == 0 ? 0 : 32 - __builtin_clz((unsigned)F), m = R >> (l + 1);
+    constexpr int d = F < 2 ? 0 : F - (1 << (l - 1));
+    unroll<0, (l == 0 ? 1 : 2)>([&](auto s_) {
+        constexpr int c = 2 * d + decltype(s_)::value;
+        unroll<0, m>([&](auto j_) {
+            constexpr int j = decltype(j_)::value;
+            if constexpr (decltype(s_)::value == 0)
+                butterfly(x[2 * m * c + j], x[2 * m * c + j + m], t.x, t.y);
+            else
+                butterfly(x[2 * m * c + j], x[2 * m * c + j + m], -t.y, t.x);
+        });
+    });
+}
+
 // Forward on R registers below a lane's own root; w[2^(l-1) + (c >> 1)] (w[0]
 // at level 0) is the twiddle of node c of level l, even c.
 template <int R, class W>

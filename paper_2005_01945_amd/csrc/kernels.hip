@@ -990,10 +990,11 @@ void k_blind_rotate_fft(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uin
 // Between the steps the accumulators are in registers and pass through the
 // same LDS to be read rotated.
 //
-// Bound by issue: about 2,360 VALU (1,860 of them f64 at 4.5-4.9 cycles) and
-// 128 matrix instructions of 16 cycles per wave and step, 13,000 of the 16,800
-// cycles that a step takes per wave at two waves per SIMD.  16,384 gates in
-// 54 ms, 2,048 in 7.4 ms, 1,024 (one wave per SIMD) in 4.8 ms; the integer
+// Bound by issue: about 2,310 VALU (1,860 of them f64 at 4.6-5.1 cycles) and
+// 128 matrix instructions of 16 cycles per wave and step, 12,800 of the 16,400
+// cycles that a step takes per wave at two waves per SIMD; LDS is busy a third
+// of the time, its writes (64 B per clock) most of it.  16,384 gates in 53 ms,
+// 2,048 in 7.2 ms, 1,024 (one wave per SIMD) in 4.5 ms; the integer
 // NTTs modulo two 28-bit primes that this replaces issued 6,570 VALU per wave
 // and step: 100, 12.5 and 8.1 ms.
 constexpr int kRowBytes = 32 * 8 + 16;  // 16-byte skew: lanes of layout B read 16 rows at once
@@ -1004,6 +1005,20 @@ struct alignas(4096) GroupLds {
     cd tabi[32][16];            // inverse factor of coefficient t, block Q
 };
 static_assert(2 * sizeof(GroupLds) <= 160 * 1024, "two groups per compute unit");
+
+constexpr int kStaged = 12;  // key loads of a step that go through LDS
+constexpr int KW = 8;        // window of the others, in registers
+static_assert(kStaged % 4 == 0 && kStaged * 1024 <= 64 * kRowBytes, "staged keys fit the wave's own rows");
+static_assert(3 * 64 * kRowBytes + kStaged * 1024 <= 65536, "and below 64 KB of LDS");
+
+// Starts the copy of 1 KB of key (the lanes' 16 bytes at byte offset `off`)
+// from memory to LDS byte address `dst`, which must be below 64 KB (M0 holds
+// its low 16 bits; the compiler keeps nothing in M0).  The compiler does not count the copy: the reader waits
+// for every load (vmcnt(0)) before it reads the bytes.
+__device__ __forceinline__ void load_key_lds(const cd* __restrict__ src, uint32_t off, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 ::"s"(dst), "v"(off), "s"(src) : "memory");
+}
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
@@ -1042,7 +1057,11 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
     char* rowB = buf + (64 * w + lane) * kRowBytes;            // layout B: this lane's row
     const cd* tf = &S.tabf[0][4 * w + b];
     const cd* ti = &S.tabi[0][4 * w + b];
-    const cd* key = K.bkc + 64 * w + lane;
+    const cd* keyw = K.bkc + 64 * w;  // this wave's keys of the step
+    const cd* key = keyw + lane;
+    const uint32_t lane16 = 16 * lane;
+    const uint32_t kslot = (uint32_t)(uintptr_t)(const lds_u32*)(const uint32_t*)(buf + 64 * w * kRowBytes);
+    const char* kread = buf + 64 * w * kRowBytes + 16 * lane;
     const uint32_t abase = (uint32_t)(uintptr_t)(const lds_u32*)accl[h];
     auto col_at = [&](auto d, auto q) -> double& {
         constexpr int Q = decltype(q)::value;
@@ -1097,32 +1116,48 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
             y[2 * k].y = v.x;
             y[2 * k + 1].y = v.y;
         }
-        constexpr int KW = 4;  // key loads in flight
-        cd kb[KW];
+        lds_barrier();  // every wave has read the imaginary parts
+        // The multiply-add wants its 32 KB of key a memory latency (1,000
+        // cycles under this load) early and has registers for eight of its 32
+        // loads: the first twelve wait in the wave's own rows, idle until the
+        // inverse exchange, while the transform runs (12 staged and a window
+        // of 8: 13.65 ms at 4,096 gates; a window of 4 and none staged, 14.0;
+        // all staged, 14.1; a window of 8 and none staged spills, 14.8).
 #pragma unroll
-        for (int k = 0; k < KW; ++k) kb[k] = key[k * 256];
-        sched_fence();
+        for (int k = 0; k < kStaged; ++k) load_key_lds(keyw + k * 256, lane16, kslot + 1024 * k);
         fft::forward_lane<32>(y, [&](auto k) { return tf[16 * decltype(k)::value]; });
         // out_o = sum over rows of K_(r, o) x_r, per leaf: matrix products of
         // 4 outputs x 4 rows x 4 gates, four leaves (b) per instruction
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        cd kr[KW];
 #pragma unroll
-        for (int c = 0; c < 32; c += 4) {
+        for (int k = 0; k < KW; ++k) kr[k] = key[(kStaged + k) * 256];
+        sched_fence();
+        static_for<0, 8>([&](auto C_) {
+            constexpr int c = 4 * decltype(C_)::value;
+            cd kb[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if constexpr (c < kStaged) kb[k] = *reinterpret_cast<const cd*>(kread + 1024 * (c + k));
+                else kb[k] = kr[(c + k - kStaged) % KW];
+            }
             double re[4], im[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[(c + k) % KW].x, y[c + k].x, 0.0, 0, 0, 0);
+            for (int k = 0; k < 4; ++k) re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[k].x, y[c + k].x, 0.0, 0, 0, 0);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[(c + k) % KW].x, y[c + k].y, 0.0, 0, 0, 0);
+            for (int k = 0; k < 4; ++k) im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[k].x, y[c + k].y, 0.0, 0, 0, 0);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[(c + k) % KW].y, y[c + k].y, re[k], 0, 0, 1);
+            for (int k = 0; k < 4; ++k) re[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[k].y, y[c + k].y, re[k], 0, 0, 1);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[(c + k) % KW].y, y[c + k].x, im[k], 0, 0, 0);
+            for (int k = 0; k < 4; ++k) im[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(kb[k].y, y[c + k].x, im[k], 0, 0, 0);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 y[c + k] = {re[k], im[k]};
-                if (c + k + KW < 32) kb[(c + k) % KW] = key[(c + k + KW) * 256];
+                if constexpr (c >= kStaged && c + KW < 32) kr[(c + k - kStaged) % KW] = key[(c + k + KW) * 256];
             }
             sched_fence();
-        }
+        });
+        keyw += kKeyStep;
         key += kKeyStep;
         fft::inverse_root<32>(y);
 #pragma unroll
@@ -1130,7 +1165,6 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
             const cd f = ti[16 * m];
             y[m] = {__builtin_fma(f.x, y[m].x, -(f.y * y[m].y)), __builtin_fma(f.x, y[m].y, f.y * y[m].x)};
         }
-        lds_barrier();  // every wave has read the imaginary parts
 #pragma unroll
         for (int k = 0; k < 16; ++k) *reinterpret_cast<cd*>(rowB + 16 * k) = {y[2 * k].x, y[2 * k + 1].x};
         lds_barrier();
