@@ -54,10 +54,12 @@ struct DeviceKeys {
     const uint8_t* ksb;       // KSK rows v = 1..3 as byte limbs in matrix-operand order (50 MB)
     const uint64_t* twf;      // forward twiddles [32][32]
     const uint64_t* twi;      // inverse twiddles (with N^-1) [32][32]
-    // FFT products: BK halves at the leaves in the two kernels' layouts (65.5
-    // MB each) and the roots E(k) = exp(i pi k / 1024), k < 2048.
+    // FFT products: BK halves at the leaves in the layouts of the kernels with
+    // two waves per gate, groups and eight waves per gate (65.5 MB each) and
+    // the roots E(k) = exp(i pi k / 1024), k < 2048.
     const fft::cd* bkw;
     const fft::cd* bkc;
+    const fft::cd* bkn;
     const fft::cd* roots;
 };
 
@@ -68,8 +70,8 @@ constexpr int kKeyStep = 4 * 4 * 512;
 // BK (uint32 [n][2l][2][N], device) -> NTT-domain kernel layout.
 hipError_t launch_bk_prepare(const uint32_t* bk, uint64_t* bkd, const uint64_t* twf,
                              uint32_t n_lwe, hipStream_t s);
-// The same to the FFT domain (either layout may be null).
-hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc, const fft::cd* roots,
+// The same to the FFT domain (any layout may be null).
+hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc, fft::cd* bkn, const fft::cd* roots,
                                  uint32_t n_lwe, hipStream_t s);
 
 // Kernel shape of a blind-rotation launch.  arith: 0 = NTT over the Goldilocks
@@ -78,7 +80,8 @@ hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc,
 //     {1, 2, 4, 8} gates share a workgroup (and its twiddle copy in LDS);
 //     waves_per_gate = 2: two waves split each CMux of one gate.
 //   arith 1: waves_per_gate = 1: groups of four gates on four waves, whatever
-//     gates_per_group; waves_per_gate = 2 or 4: that many waves per gate.
+//     gates_per_group; waves_per_gate = 2: two waves per gate; waves_per_gate =
+//     4: the lowest-latency shape, eight waves per gate, two per digit row.
 // Every shape gives the same words.
 struct LaunchConfig {
     uint32_t waves_per_gate;
@@ -101,7 +104,7 @@ hipError_t launch_key_switch(const DeviceKeys& K, const GateIO& io, const uint32
                              uint32_t count, hipStream_t s);
 
 // One CMux on acc[2][N] (device) with prepared BK_i (one iteration of bkd
-// for arith 0, of K.bkw for arith 1).
+// for arith 0, K.bkn for arith 1).
 hipError_t launch_debug_cmux(const DeviceKeys& K, int arith, const uint64_t* bk_i, int32_t abar,
                              uint32_t* acc, hipStream_t s);
 

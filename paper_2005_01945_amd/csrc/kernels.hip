@@ -449,11 +449,9 @@ __device__ __forceinline__ uint32_t digit_word(uint32_t v, uint32_t own, int d4)
     return (((v + sgn) ^ sgn) + (kDecompOffset - own)) ^ 0x80200000u;
 }
 
-// Digit rows of polynomial a: coefficient lane + 64 e, e < 8 real, else
-// imaginary part of register e mod 8.  ND = 2: both digits; ND = 1: the digit
-// whose field starts at bit `shift`.
-template <int ND>
-__device__ __forceinline__ void wave_digits(const uint32_t* a, int ai, int shift, int lane, cd (&x)[ND][8]) {
+// Both digit rows of polynomial a: coefficient lane + 64 e, e < 8 real, else
+// imaginary part of register e mod 8.
+__device__ __forceinline__ void wave_digits(const uint32_t* a, int ai, int lane, cd (&x)[2][8]) {
     const lds_u32* am = lds_column(a, lane);
     const uint32_t abase = (uint32_t)(uintptr_t)(const lds_u32*)a;
     const int d4 = 4 * (lane - ai);
@@ -467,8 +465,8 @@ __device__ __forceinline__ void wave_digits(const uint32_t* a, int ai, int shift
     for (int e = 0; e < 16; ++e) {
         const uint32_t z = digit_word(v[e], own[e], d4 + 256 * e);
 #pragma unroll
-        for (int d = 0; d < ND; ++d) {
-            const double dg = (double)(int32_t)__builtin_amdgcn_sbfe((int32_t)z, ND == 2 ? 22 - 10 * d : shift, 10);
+        for (int d = 0; d < 2; ++d) {
+            const double dg = (double)(int32_t)__builtin_amdgcn_sbfe((int32_t)z, 22 - 10 * d, 10);
             if (e < 8)
                 x[d][e & 7].x = dg;
             else
@@ -494,12 +492,11 @@ __device__ __forceinline__ void lds_add(uint32_t* p, uint32_t v) {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// LDS of a gate on W wavefronts: accumulator, each wave's exchange slots, the
+// LDS of a gate on two wavefronts: accumulator, each wave's exchange slots, the
 // twist factors and the digit spectra that the waves share.
-template <int W>
-struct alignas(4096) FftLds {
+struct alignas(4096) PairFftLds {
     uint32_t acc[2][1024];
-    cd ex[W][kExSlots];
+    cd ex[2][kExSlots];
     cd tw[512];
     cd spec[4][512];
 };
@@ -509,79 +506,303 @@ __device__ __forceinline__ const cd* key_row(const cd* __restrict__ key, int r, 
     return key + ((r * 4 + o) * 8) * 64 + lane;
 }
 
-// Keys of a gate on four wavefronts: the wave's whole share of a step (rows x
-// registers), each row reloaded for the next step as soon as it is used.
-struct KeyAhead {
-    cd row[4][8];
-};
-
 __device__ __forceinline__ void load_key_row(cd (&k)[8], const cd* __restrict__ key, int r, int o, int lane) {
     const cd* p = key_row(key, r, o, lane);
 #pragma unroll
     for (int j = 0; j < 8; ++j) k[j] = p[64 * j];
 }
 
-// One CMux step of a gate on W = 2 or 4 wavefronts.  Wave w transforms rows
-// (4 / W) w ... and finishes outputs (4 / W) w ...; the rows' spectra meet in
-// LDS.  Two barriers per step: spectra written, ACC updated.  With W = 4 the
-// step's keys are in `ka` and those of the next step (next) are loaded.
-template <int W>
-__device__ __forceinline__ void fft_step(FftLds<W>& S, int ai, const cd* __restrict__ key, const cd* __restrict__ next,
-                                         KeyAhead& ka, const LaneTwiddles& T, int wave, int lane) {
-    constexpr int RP = 4 / W;
-    uint32_t (&acc)[2][1024] = S.acc;
+// One CMux step of a gate on two wavefronts.  Wave w transforms rows 2 w and
+// 2 w + 1 (both digits of polynomial w) and finishes outputs 2 w and 2 w + 1
+// (both halves of column w); the rows' spectra meet in LDS.  Two barriers per
+// step: spectra written, ACC updated.
+__device__ __forceinline__ void pair_step(PairFftLds& S, int ai, const cd* __restrict__ key, const LaneTwiddles& T,
+                                          int wave, int lane) {
     cd* ex = S.ex[wave];
-    cd pre[RP][2][8];  // W = 2: keys of rows 0 and 1, on their way during the transforms
-    if constexpr (W == 2) {
+    cd pre[2][2][8];  // keys of rows 0 and 1, on their way during the transforms
 #pragma unroll
-        for (int k = 0; k < RP; ++k)
+    for (int k = 0; k < 2; ++k)
 #pragma unroll
-            for (int r = 0; r < 2; ++r) load_key_row(pre[k][r], key, r, RP * wave + k, lane);
-        sched_fence();
-    }
-    cd x[RP][8];
-    if constexpr (W == 4)
-        wave_digits<1>(acc[wave >> 1], ai, 22 - 10 * (wave & 1), lane, x);
-    else
-        wave_digits<2>(acc[wave], ai, 0, lane, x);
+        for (int r = 0; r < 2; ++r) load_key_row(pre[k][r], key, r, 2 * wave + k, lane);
+    sched_fence();
+    cd x[2][8];
+    wave_digits(S.acc[wave], ai, lane, x);
 #pragma unroll
-    for (int k = 0; k < RP; ++k) {
+    for (int k = 0; k < 2; ++k) {
         fft512_forward(x[k], ex, T, lane);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) S.spec[RP * wave + k][64 * j + lane] = x[k][j];
+        for (int j = 0; j < 8; ++j) S.spec[2 * wave + k][64 * j + lane] = x[k][j];
     }
-    lds_barrier();  // spectra written; every wave has read ACC
-    cd out[RP][8];
+    lds_barrier();  // spectra written; both waves have read ACC
+    cd out[2][8];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const cd v = S.spec[r][64 * j + lane];
 #pragma unroll
-            for (int k = 0; k < RP; ++k) {
+            for (int k = 0; k < 2; ++k) {
                 if (r == 0) out[k][j] = {0.0, 0.0};
-                mac(out[k][j],
-                    W == 4 ? ka.row[r][j] : r < 2 ? pre[k][r & 1][j] : key_row(key, r, RP * wave + k, lane)[64 * j], v);
+                mac(out[k][j], r < 2 ? pre[k][r & 1][j] : key_row(key, r, 2 * wave + k, lane)[64 * j], v);
             }
         }
-        if constexpr (W == 4) {
-            load_key_row(ka.row[r], next, r, wave, lane);
-            sched_fence();
+    }
+    uint32_t lo[16], hi[16];
+    fft512_inverse(out[0], ex, T, lane);
+    finish_words(out[0], S.tw, lane, lo);
+    fft512_inverse(out[1], ex, T, lane);
+    finish_words(out[1], S.tw, lane, hi);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) lds_add(&S.acc[wave][lane + 64 * e], lo[e] + (hi[e] << 16));
+    lds_barrier();  // ACC updated; spectra free
+}
+
+// ---------------------------------------------------------------------------
+// One gate on eight wavefronts, two per digit row (and per output): wave
+// (row, half) keeps the half of the ring X^512 - i = (X^256 - w)(X^256 + w),
+// w = E(256), i.e. 256 of a row's leaves, four registers per lane.  The four
+// waves of a polynomial share its digit words; both waves of a row fold its
+// digits by the first split, and the other eight levels are four passes of two
+// levels in registers.  Registers and lane
+// bits are exchanged between the passes: bits 5, 4 by v_permlane32/16_swap,
+// bits 3, 2 and bits 1, 0 through the wave's slots in LDS.  The last level of
+// the inverse joins the two halves through LDS.
+// ---------------------------------------------------------------------------
+
+constexpr int kNarrowSlots = 320;
+constexpr int kPad = 64;  // words before each accumulator polynomial: -ACC[960 + k]
+
+struct alignas(16) NarrowLds {
+    uint32_t acc[2][kPad + 1024];
+    uint32_t tail[kPad];  // (makes the padded view below end inside the struct)
+    uint4 digits[2][4][64];  // digit words of coefficients lane + 64 (4 part + word)
+    cd ex[8][kNarrowSlots];
+    cd spec[4][2][256];
+    cd tw[2][256];  // [half]: E(-j), E(-5 j)
+    // The accumulator polynomials behind their pads.
+    __device__ __forceinline__ uint32_t (&view())[2][kPad + 1024] {
+        return *reinterpret_cast<uint32_t (*)[2][kPad + 1024]>(&acc[0][kPad]);
+    }
+};
+
+struct NarrowTwiddles {
+    cd f1[2];                     // pass 1, the same for the whole wave
+    cd f2[2], f3[2], f4[2];       // forward passes 2..4
+    cd i2[2], i3[2], i4[2];       // inverse passes 2..4 (conjugates)
+};
+
+__device__ __forceinline__ void load_narrow_twiddles(NarrowTwiddles& T, const cd* __restrict__ roots, int half,
+                                                     int lane) {
+    const int p2 = half + 2 * ((lane >> 5) & 1) + 4 * ((lane >> 4) & 1);
+    const int p3 = p2 + 8 * ((lane >> 3) & 1) + 16 * ((lane >> 2) & 1);
+    const int p4 = p3 + 32 * ((lane >> 1) & 1) + 64 * (lane & 1);
+    T.f1[0] = roots[128 + 512 * half], T.f1[1] = roots[64 + 256 * half];
+    T.f2[0] = roots[32 + 128 * p2], T.f2[1] = roots[16 + 64 * p2];
+    T.f3[0] = roots[8 + 32 * p3], T.f3[1] = roots[4 + 16 * p3];
+    T.f4[0] = roots[2 + 8 * p4], T.f4[1] = roots[1 + 4 * p4];
+    T.i2[0] = conj_root(roots, 256 * (lane & 3)), T.i2[1] = conj_root(roots, 128 * (lane & 3));
+    T.i3[0] = conj_root(roots, 64 * (lane & 15)), T.i3[1] = conj_root(roots, 32 * (lane & 15));
+    T.i4[0] = conj_root(roots, 16 * lane), T.i4[1] = conj_root(roots, 8 * lane);
+}
+
+__device__ __forceinline__ double with_words(uint32_t lo, uint32_t hi) {
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Exchanges the register bit that tells a from b with lane bit 5 (ROW16: 4).
+template <bool ROW16>
+__device__ __forceinline__ void lane_swap(double& a, double& b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    if constexpr (ROW16) {
+        const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+        a = with_words(l[0], h[0]);
+        b = with_words(l[1], h[1]);
+    } else {
+        const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+        a = with_words(l[0], h[0]);
+        b = with_words(l[1], h[1]);
+    }
+}
+
+// Register bits (1, 0) <-> lane bits (5, 4).
+__device__ __forceinline__ void exchange_high(cd (&x)[4]) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        lane_swap<false>(x[k].x, x[k + 2].x);
+        lane_swap<false>(x[k].y, x[k + 2].y);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k += 2) {
+        lane_swap<true>(x[k].x, x[k + 1].x);
+        lane_swap<true>(x[k].y, x[k + 1].y);
+    }
+}
+
+// Two levels on four registers below a node: w[0] splits it, w[1] its even
+// child (the odd child's twiddle is i w[1]).
+__device__ __forceinline__ void forward4(cd (&x)[4], const cd (&w)[2]) {
+    fft::butterfly(x[0], x[2], w[0].x, w[0].y);
+    fft::butterfly(x[1], x[3], w[0].x, w[0].y);
+    fft::butterfly(x[0], x[1], w[1].x, w[1].y);
+    fft::butterfly(x[2], x[3], -w[1].y, w[1].x);
+}
+
+__device__ __forceinline__ void inverse4(cd (&x)[4], const cd (&w)[2]) {
+    fft::butterfly(x[0], x[1], w[0].x, w[0].y);
+    fft::butterfly(x[2], x[3], w[0].x, w[0].y);
+    fft::butterfly(x[0], x[2], w[1].x, w[1].y);
+    fft::butterfly(x[1], x[3], w[1].y, -w[1].x);
+}
+
+template <int WS, int RS>
+__device__ __forceinline__ void exchange_low(cd (&x)[4], cd* wbase, const cd* rbase) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) wbase[WS * k] = x[k];
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = rbase[RS * k];
+    wave_lds_sync();
+}
+
+// Key words of row r, output o, half, register j, lane (narrow layout).
+__device__ __forceinline__ void load_narrow_keys(cd (&k)[4], const cd* __restrict__ key, int r, int o, int half,
+                                                 int lane) {
+    const cd* p = key + (((r * 4 + o) * 2 + half) * 4) * 64 + lane;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) k[j] = p[64 * j];
+}
+
+// One CMux step of wave (row, half).  ka[k]: the step's keys of row (row + k)
+// mod 4; k = 0, 1 are loaded a step ahead (from `next`), k = 2, 3 during the
+// forward transform.  Four barriers: digits written, spectra written, halves
+// joined, ACC updated.
+__device__ __forceinline__ void narrow_step(NarrowLds& S, int ai, const cd* __restrict__ cur,
+                                            const cd* __restrict__ next, cd (&ka)[4][4], const NarrowTwiddles& T,
+                                            int row, int half, int lane) {
+    cd* ex = S.ex[2 * row + half];
+    const int u = lane >> 2, v = lane & 3, h4 = lane >> 4;
+    cd* e2a = ex + 80 * h4 + (lane & 15);                  // bits 3, 2: stride 20 by register,
+    cd* e2b = ex + 80 * h4 + 20 * (u & 3) + v;             // stride 4 after the exchange
+    cd* e3a = ex + 20 * u + v;                             // bits 1, 0: stride 5,
+    cd* e3b = ex + 20 * u + 5 * v;                         // stride 1
+    cd x[4];
+    {
+        // D = X^ai ACC - ACC, four words per lane and wave: the four waves of
+        // a polynomial share them through LDS.  Coefficient lane + 64 e reads
+        // block (e - ai / 64) mod 16 at lane - ai mod 64 (the pad serves
+        // negative ones), negated when (e - ai / 64) mod 32 >= 16, the same
+        // for the whole wave.
+        const int hp = row >> 1, part = 2 * (row & 1) + half;
+        const uint32_t* a = S.view()[hp];
+        const lds_u32* am = lds_column(a + 256 * part, lane);
+        const uint32_t rot = (uint32_t)(uintptr_t)(const lds_u32*)a + 4 * (uint32_t)(lane - (ai & 63));
+        const uint32_t first = (4u * part - ((uint32_t)ai >> 6)) << 8;
+        uint32_t w[4], own[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            w[e] = *(const lds_u32*)(uintptr_t)(rot + ((first + 256u * e) & 0xF00u));
+            own[e] = am[64 * e];
+        }
+        uint32_t z[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t sgn = (uint32_t)((int32_t)((first + 256u * e) << 19) >> 31);
+            z[e] = ((w[e] ^ sgn) + (kDecompOffset - sgn - own[e])) ^ 0x80200000u;
+        }
+        S.digits[hp][part][lane] = make_uint4(z[0], z[1], z[2], z[3]);
+        lds_barrier();  // digit words written; every wave has read ACC
+        const int shift = 22 - 10 * (row & 1);
+        int32_t d[16];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint4 q = S.digits[hp][e][lane];
+            d[4 * e + 0] = (int32_t)__builtin_amdgcn_sbfe((int32_t)q.x, shift, 10);
+            d[4 * e + 1] = (int32_t)__builtin_amdgcn_sbfe((int32_t)q.y, shift, 10);
+            d[4 * e + 2] = (int32_t)__builtin_amdgcn_sbfe((int32_t)q.z, shift, 10);
+            d[4 * e + 3] = (int32_t)__builtin_amdgcn_sbfe((int32_t)q.w, shift, 10);
+        }
+        // first split: a + w b or a - w b with w = (1 + i) / sqrt 2
+        const double c = half ? -fft::kCos[8] : fft::kCos[8];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            x[k].x = __builtin_fma(c, (double)(d[k + 4] - d[k + 12]), (double)d[k]);
+            x[k].y = __builtin_fma(c, (double)(d[k + 4] + d[k + 12]), (double)d[k + 8]);
         }
     }
-    uint32_t v[RP][16];
+    load_narrow_keys(ka[2], cur, (row + 2) & 3, row, half, lane);
+    sched_fence();
+    forward4(x, T.f1);
+    exchange_high(x);
+    forward4(x, T.f2);
+    exchange_low<20, 4>(x, e2a, e2b);
+    load_narrow_keys(ka[3], cur, (row + 3) & 3, row, half, lane);
+    sched_fence();
+    forward4(x, T.f3);
+    exchange_low<5, 1>(x, e3a, e3b);
+    forward4(x, T.f4);
 #pragma unroll
-    for (int k = 0; k < RP; ++k) {
-        fft512_inverse(out[k], ex, T, lane);
-        finish_words(out[k], S.tw, lane, v[k]);
+    for (int j = 0; j < 4; ++j) S.spec[row][half][64 * j + lane] = x[j];
+    lds_barrier();  // spectra written
+    cd out[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (k == 0) out[j] = {0.0, 0.0};
+            mac(out[j], ka[k][j], k == 0 ? x[j] : S.spec[(row + k) & 3][half][64 * j + lane]);
+        }
     }
-    if constexpr (W == 4) {
+    sched_fence();
+    fft::inverse_root<4>(out);
+    exchange_low<1, 5>(out, e3b, e3a);
+    load_narrow_keys(ka[0], next, (row + 0) & 3, row, half, lane);
+    sched_fence();
+    inverse4(out, T.i2);
+    exchange_low<4, 20>(out, e2b, e2a);
+    inverse4(out, T.i3);
+    exchange_high(out);
+    inverse4(out, T.i4);
+    load_narrow_keys(ka[1], next, (row + 1) & 3, row, half, lane);
+    sched_fence();
+    // last level and twist: with e = E(-j) even_j and o = E(-5 j) odd_j, the
+    // outputs are e + o at j = lane + 64 q and (e - o) E(-256) at j + 256
 #pragma unroll
-        for (int e = 0; e < 16; ++e) lds_add(&acc[wave >> 1][lane + 64 * e], v[0][e] << (16 * (wave & 1)));
+    for (int q = 0; q < 4; ++q) {
+        const cd f = S.tw[half][64 * q + lane], y = out[q];
+        out[q] = {__builtin_fma(f.x, y.x, -(f.y * y.y)), __builtin_fma(f.x, y.y, f.y * y.x)};
+        ex[64 * q + lane] = out[q];
+    }
+    lds_barrier();
+    const cd* other = S.ex[2 * row + (half ^ 1)];
+    const int o = row;
+    uint32_t* accw = &S.view()[o >> 1][lane + 256 * half];
+    uint32_t w[8];
+    if (half == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const cd y = other[64 * q + lane];
+            w[q] = fft::round_word(out[q].x + y.x);
+            w[q + 4] = fft::round_word(out[q].y + y.y);
+        }
     } else {
+        constexpr double c = fft::kCos[8];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) lds_add(&acc[wave][lane + 64 * e], v[0][e] + (v[RP - 1][e] << 16));
+        for (int q = 0; q < 4; ++q) {
+            const cd y = other[64 * q + lane];
+            const double dx = y.x - out[q].x, dy = y.y - out[q].y;
+            w[q] = fft::round_word(c * (dx + dy));
+            w[q + 4] = fft::round_word(c * (dy - dx));
+        }
     }
+    const int sh = 16 * (o & 1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        lds_add(accw + 64 * q, w[q] << sh);
+        lds_add(accw + 64 * q + 512, w[q + 4] << sh);
+    }
+    if (half == 1) lds_add(&S.acc[o >> 1][lane], 0u - (w[7] << sh));
     lds_barrier();  // ACC updated; spectra free
 }
 
@@ -686,12 +907,6 @@ __device__ __forceinline__ uint32_t* ks_output(const GateIO& io, uint32_t k) {
     return io.ops1 ? io.out1 + (size_t)g * NW : nullptr;
 }
 
-template <int THREADS>
-__device__ __forceinline__ void load_twist(cd* tw, const cd* __restrict__ roots) {
-    for (int k = threadIdx.x; k < 512; k += THREADS) tw[k] = conj_root(roots, k);
-    __syncthreads();
-}
-
 template <int THREADS, class L>
 __device__ __forceinline__ void load_twiddles(L& S, const uint64_t* twf, const uint64_t* twi) {
     for (int k = threadIdx.x; k < 1024; k += THREADS) {
@@ -742,7 +957,8 @@ __device__ __forceinline__ uint32_t gate_mu(const GateIO& io, uint32_t g) {
 // X^(N-1)).  Lane l = 32h + t writes coefficients t + 32q of polynomial h.
 // With a test vector tv (programmable bootstrapping): ACC = (0, X^c tv),
 // coefficient m = tv[j] for j = (m - c) mod 2N < N, else -tv[j - N].
-__device__ __forceinline__ void acc_init(uint32_t (&acc)[2][1024], int bbar, int h, int t,
+template <int S>
+__device__ __forceinline__ void acc_init(uint32_t (&acc)[2][S], int bbar, int h, int t,
                                          const uint32_t* __restrict__ tv, uint32_t mu) {
     const int c = (2 * N - bbar) & (2 * N - 1);
     if (tv) {
@@ -775,8 +991,8 @@ __device__ __forceinline__ uint32_t pack_kept(uint32_t even, uint32_t odd) {
 
 // Sample extraction of coefficient 0: a'_0 = a_0, a'_m = -a_(N-m), b' = b_0,
 // by THREADS threads with index `tid`.
-template <int THREADS>
-__device__ __forceinline__ void sample_extract(const uint32_t (&acc)[2][1024], uint32_t* o, int tid) {
+template <int THREADS, int S>
+__device__ __forceinline__ void sample_extract(const uint32_t (&acc)[2][S], uint32_t* o, int tid) {
     for (int q = tid; q < N / 2; q += THREADS)
         o[q] = pack_kept(q == 0 ? acc[0][0] : 0u - acc[0][N - 2 * q], 0u - acc[0][N - 2 * q - 1]);
     if (tid == 0) o[N / 2] = acc[1][0];
@@ -789,8 +1005,8 @@ __device__ __forceinline__ void sample_extract(const uint32_t (&acc)[2][1024], u
 // with values g0, g1, g2 (+-1, units of 1/8) is the sample
 // (g1 - g2) E1 + (g1 - g0) E2 + (0, (g0 + g2)/16).  Extraction of
 // coefficient m: a'_j = a_(m-j) for j <= m, -a_(N+m-j) for j > m, b' = b_m.
-template <int THREADS>
-__device__ __forceinline__ void compound_extract(const uint32_t (&acc)[2][1024], uint32_t op0, uint32_t op1,
+template <int THREADS, int S>
+__device__ __forceinline__ void compound_extract(const uint32_t (&acc)[2][S], uint32_t op0, uint32_t op1,
                                                  uint32_t* o0, uint32_t* o1, int tid) {
     constexpr int m1 = 3 * N / 4, m2 = N / 4;
     const int32_t a0 = sym_value(op0, 0), a1 = sym_value(op0, 1), a2 = sym_value(op0, 2);
@@ -820,8 +1036,8 @@ __device__ __forceinline__ void compound_extract(const uint32_t (&acc)[2][1024],
 // After the blind rotation: the extracted sample(s) of gate g into its
 // slot(s) of big; an invalid code gives all-zero samples (which key-switch
 // to the all-zero output) and is reported through io.err.
-template <int THREADS>
-__device__ __forceinline__ void gate_epilogue(const GateIO& io, uint32_t g, const uint32_t (&acc)[2][1024],
+template <int THREADS, int S>
+__device__ __forceinline__ void gate_epilogue(const GateIO& io, uint32_t g, const uint32_t (&acc)[2][S],
                                               uint32_t* __restrict__ big, int tid) {
     const GateMode m = gate_mode(io, g);
     uint32_t* o = big + (size_t)(io.pair_slots ? 2 * g : g) * kSampleWords;
@@ -925,25 +1141,20 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     gate_epilogue<128>(io, g, S.acc, big, threadIdx.x);
 }
 
-// Blind rotation with FFT products, W = 2 or 4 wavefronts per gate, for
-// batches that leave compute units with one gate or two.  Bound by latency:
-// at one gate per compute unit a CMux step takes 4.4 us (W = 4) for 830 VALU
-// instructions per wave, about 40% of the issue rate; the rest is the LDS
-// exchanges and two barriers.  With W = 4 the key words of a step are loaded
-// one whole step ahead into 128 registers (loading half of them at the start
-// of the step and half after the transforms: 7.8 us), so this shape runs one
-// wave per SIMD.  256 gates: 2.2 ms with W = 4, 2.7 ms with W = 2; 512 gates:
-// 4.4 ms and 3.0 ms (the integer NTTs modulo two primes that this replaces:
-// 3.3 ms at 256, 4.6 ms at 512).
-template <int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(1, W == 4 ? 1 : 2)))
-void k_blind_rotate_fft(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
-    __shared__ FftLds<W> S;
+// Blind rotation with FFT products on two wavefronts per gate, for batches of
+// one to two gates per compute unit.  Bound by latency, of the LDS exchanges
+// and of the key loads of rows 2 and 3 (registers hold those of two rows):
+// 512 gates in 3.2 ms, 256 in 2.7 ms (the integer NTTs modulo two primes that
+// this replaces: 4.6 and 4.4 ms).  Loading all four rows at the start of the
+// step needs 128 accumulation registers and as many moves: 3.3 ms at 512.
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 2)))
+void k_blind_rotate_fft_pair(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
+    __shared__ PairFftLds S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, h = lane >> 5, t = lane & 31;
-    load_twist<64 * W>(S.tw, K.roots);
     const uint32_t g = blockIdx.x;
     if (g >= count) return;  // uniform over the block
+    for (int k = threadIdx.x; k < 512; k += 128) S.tw[k] = conj_root(K.roots, k);
     LaneTwiddles T;
     load_forward_twiddles(T, K.roots, lane);
     load_inverse_twiddles(T, K.roots, lane);
@@ -951,24 +1162,69 @@ void k_blind_rotate_fft(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uin
     const int bbar = gate_prologue(io, g, lane, ab);
     if (wave == 0) acc_init(S.acc, bbar, h, t, io.tv, gate_mu(io, g));
     const cd* key = K.bkw;
-    KeyAhead ka;
-    if constexpr (W == 4) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) load_key_row(ka.row[r], key, r, wave, lane);
-    }
     __syncthreads();
 #pragma unroll 1
     for (int i = 0; i < NLWE; ++i) {
         const int ai = __builtin_amdgcn_readlane(ab[0], i & 63);
-        const cd* next = i + 1 < NLWE ? key + kKeyStep : key;
-        fft_step<W>(S, ai, key, next, ka, T, wave, lane);
-        key = next;
+        pair_step(S, ai, key, T, wave, lane);
+        key += kKeyStep;
         if ((i & 63) == 63) {
 #pragma unroll
             for (int r = 0; r < 7; ++r) ab[r] = ab[r + 1];
         }
     }
-    gate_epilogue<64 * W>(io, g, S.acc, big, threadIdx.x);
+    gate_epilogue<128>(io, g, S.acc, big, threadIdx.x);
+}
+
+// Blind rotation with FFT products on eight wavefronts per gate, for the
+// lowest latency: one gate in 1.65 ms, 256 in 1.9 ms.  A step's 7,900 cycles
+// are a chain of ten LDS round trips and four barriers around 430 VALU per
+// wave; two waves per SIMD fill each other's gaps (four wavefronts per gate,
+// one per row, with the same arithmetic: 2.06 and 2.24 ms; the integer NTTs
+// modulo two primes before that: 3.2 and 3.3 ms).  The 128 KB of key per step
+// are 2,000 cycles of the vector memory path, so the loads are spread over the
+// step: all in one place they delayed it to 2.0 ms.
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
+    __shared__ NarrowLds S;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = wave >> 1, half = wave & 1;
+    const int lane = threadIdx.x & 63, h = lane >> 5, t = lane & 31;
+    const uint32_t g = blockIdx.x;
+    if (g >= count) return;  // uniform over the block
+    {
+        const int hf = threadIdx.x >> 8, j = threadIdx.x & 255;
+        S.tw[hf][j] = conj_root(K.roots, hf ? 5 * j : j);
+    }
+    NarrowTwiddles T;
+    load_narrow_twiddles(T, K.roots, half, lane);
+    uint32_t ab[8];
+    const int bbar = gate_prologue(io, g, lane, ab);
+    uint32_t (&acc)[2][kPad + 1024] = S.view();
+    if (wave == 0) {
+        acc_init(acc, bbar, h, t, io.tv, gate_mu(io, g));
+        wave_lds_sync();
+#pragma unroll
+        for (int p = 0; p < 2; ++p) S.acc[p][lane] = 0u - acc[p][960 + lane];
+    }
+    const cd* key = K.bkn;
+    cd ka[4][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) load_narrow_keys(ka[k], key, (row + k) & 3, row, half, lane);
+    __syncthreads();
+#pragma unroll 1
+    for (int b = 0; b < NLWE; b += 64) {
+#pragma unroll 1
+        for (int i = 0; i < 64 && b + i < NLWE; ++i) {
+            const int ai = __builtin_amdgcn_readlane(ab[0], i);
+            const cd* next = b + i + 1 < NLWE ? key + kKeyStep : key;
+            narrow_step(S, ai, key, next, ka, T, row, half, lane);
+            key = next;
+        }
+#pragma unroll
+        for (int r = 0; r < 7; ++r) ab[r] = ab[r + 1];
+    }
+    gate_epilogue<512>(io, g, acc, big, threadIdx.x);
 }
 
 // Blind rotation with FFT products for wide batches: groups of four gates on
@@ -1208,7 +1464,7 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
 //   bkw[i][r][o][reg][lane] (k_blind_rotate_fft), leaf 8 lane + reg;
 //   bkc[i][leaf % 32][leaf / 128][16 r + 4 (leaf / 32 % 4) + o] (k_blind_rotate_group).
 __global__ __launch_bounds__(kBlockThreads) void k_bk_prepare_fft(const uint32_t* __restrict__ bk, cd* __restrict__ bkw,
-                                                                  cd* __restrict__ bkc, const cd* __restrict__ roots,
+                                                                  cd* __restrict__ bkc, cd* __restrict__ bkn, const cd* __restrict__ roots,
                                                                   uint32_t npolys) {
     __shared__ cd ex[kWavesPerBlock][kExSlots];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1236,27 +1492,31 @@ __global__ __launch_bounds__(kBlockThreads) void k_bk_prepare_fft(const uint32_t
         for (int j = 0; j < 8; ++j) {
             const cd v = {x[j].x * (1.0 / 512), x[j].y * (1.0 / 512)};
             const uint32_t leaf = 8 * lane + j;
+            if (bkn) bkn[(size_t)i * kKeyStep + ((r * 4 + o) * 8 + 4 * (leaf / 256) + leaf % 4) * 64 + leaf % 256 / 4] = v;
             if (bkw) bkw[(size_t)i * kKeyStep + ((r * 4 + o) * 8 + j) * 64 + lane] = v;
             if (bkc) bkc[(size_t)i * kKeyStep + ((leaf % 32) * 4 + leaf / 128) * 64 + 16 * r + 4 * (leaf / 32 % 4) + o] = v;
         }
     }
 }
 
-// One CMux on acc[2][N] in global memory with the FFT products (four waves).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+// One CMux on acc[2][N] in global memory with the FFT products (eight waves).
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_debug_cmux_fft(DeviceKeys K, int32_t abar, uint32_t* __restrict__ accg) {
-    __shared__ FftLds<4> S;
+    __shared__ NarrowLds S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    LaneTwiddles T;
-    load_forward_twiddles(T, K.roots, lane);
-    load_inverse_twiddles(T, K.roots, lane);
-    KeyAhead ka;
+    const int row = wave >> 1, half = wave & 1;
+    NarrowTwiddles T;
+    load_narrow_twiddles(T, K.roots, half, lane);
+    cd ka[4][4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) load_key_row(ka.row[r], K.bkw, r, wave, lane);
-    for (int k = threadIdx.x; k < 2 * N; k += 256) S.acc[k / N][k % N] = accg[k];
-    load_twist<256>(S.tw, K.roots);
-    fft_step<4>(S, abar, K.bkw, K.bkw, ka, T, wave, lane);
-    for (int k = threadIdx.x; k < 2 * N; k += 256) accg[k] = S.acc[k / N][k % N];
+    for (int k = 0; k < 4; ++k) load_narrow_keys(ka[k], K.bkn, (row + k) & 3, row, half, lane);
+    uint32_t (&acc)[2][kPad + 1024] = S.view();
+    for (int k = threadIdx.x; k < 512; k += 512) S.tw[k >> 8][k & 255] = conj_root(K.roots, k >> 8 ? 5 * (k & 255) : k);
+    for (int k = threadIdx.x; k < 2 * N; k += 512) acc[k / N][k % N] = accg[k];
+    for (int k = threadIdx.x; k < 2 * kPad; k += 512) S.acc[k / kPad][k % kPad] = 0u - accg[k / kPad * N + 960 + k % kPad];
+    __syncthreads();
+    narrow_step(S, abar, K.bkn, K.bkn, ka, T, row, half, lane);
+    for (int k = threadIdx.x; k < 2 * N; k += 512) accg[k] = acc[k / N][k % N];
 }
 
 // Key switching N -> n: out = (0, b') - sum_{i,j} KSK[i][j][d_ij], d_ij the
@@ -1519,8 +1779,8 @@ hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* 
     if (cfg.arith == 1) {
         switch (cfg.waves_per_gate) {
         case 1: return launch(k_blind_rotate_group, 4, 256);
-        case 2: return launch(k_blind_rotate_fft<2>, 1, 128);
-        case 4: return launch(k_blind_rotate_fft<4>, 1, 256);
+        case 2: return launch(k_blind_rotate_fft_pair, 1, 128);
+        case 4: return launch(k_blind_rotate_narrow, 1, 512);
         default: return hipErrorInvalidValue;
         }
     }
@@ -1574,17 +1834,17 @@ hipError_t launch_ksk_prepare(const uint32_t* ksk, uint8_t* ksb, hipStream_t s) 
 hipError_t launch_debug_cmux(const DeviceKeys& K, int arith, const uint64_t* bk_i, int32_t abar,
                              uint32_t* acc, hipStream_t s) {
     if (arith == 1)
-        hipLaunchKernelGGL(k_debug_cmux_fft, dim3(1), dim3(256), 0, s, K, abar, acc);
+        hipLaunchKernelGGL(k_debug_cmux_fft, dim3(1), dim3(512), 0, s, K, abar, acc);
     else
         hipLaunchKernelGGL(k_debug_cmux, dim3(1), dim3(64), 0, s, K, bk_i, abar, acc);
     return hipGetLastError();
 }
 
-hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc, const fft::cd* roots,
+hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc, fft::cd* bkn, const fft::cd* roots,
                                  uint32_t n_lwe, hipStream_t s) {
     const uint32_t npolys = n_lwe * 8;
     const uint32_t blocks = (npolys + kWavesPerBlock - 1) / kWavesPerBlock;
-    hipLaunchKernelGGL(k_bk_prepare_fft, dim3(blocks), dim3(kBlockThreads), 0, s, bk, bkw, bkc, roots, npolys);
+    hipLaunchKernelGGL(k_bk_prepare_fft, dim3(blocks), dim3(kBlockThreads), 0, s, bk, bkw, bkc, bkn, roots, npolys);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 // Device context and gate-bootstrapping entry points.
 //
 // A context keeps the cloud key resident on one GPU: the bootstrapping key
-// converted once to the FFT domain (two layouts of 65.5 MB) and to the NTT
+// converted once to the FFT domain (three layouts of 65.5 MB) and to the NTT
 // domain (32.8 MB), the key-switching key as byte limbs for the int8 matrix
 // cores (50.3 MB), and the twiddle tables.  Gate batches run as two
 // launches on the caller's stream: blind rotation (with the gate prologue and
@@ -250,6 +250,8 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
         return fail(e, "bootstrapping key");
     if ((e = hipMalloc((void**)&ctx->bkc, n * dev::kKeyStep * sizeof(dev::fft::cd))) != hipSuccess)
         return fail(e, "bootstrapping key");
+    if ((e = hipMalloc((void**)&ctx->bkn, n * dev::kKeyStep * sizeof(dev::fft::cd))) != hipSuccess)
+        return fail(e, "bootstrapping key");
     if ((e = hipMalloc((void**)&ctx->roots, roots.size() * sizeof(dev::fft::cd))) != hipSuccess)
         return fail(e, "twiddles");
     if ((e = hipMalloc((void**)&ctx->ksb, kKsbBytes)) != hipSuccess) return fail(e, "key-switching key");
@@ -267,7 +269,7 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
         return fail(e, "upload");
     if ((e = dev::launch_bk_prepare(bk_tmp, ctx->bkd, ctx->twf, (uint32_t)n, ctx->stream)) != hipSuccess)
         return fail(e, "bootstrapping key transform");
-    if ((e = dev::launch_bk_prepare_fft(bk_tmp, ctx->bkw, ctx->bkc, ctx->roots, (uint32_t)n, ctx->stream)) !=
+    if ((e = dev::launch_bk_prepare_fft(bk_tmp, ctx->bkw, ctx->bkc, ctx->bkn, ctx->roots, (uint32_t)n, ctx->stream)) !=
         hipSuccess)
         return fail(e, "bootstrapping key transform");
     if ((e = dev::launch_ksk_prepare(ksk_tmp, ctx->ksb, ctx->stream)) != hipSuccess)
@@ -284,6 +286,7 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
     ctx->keys.twi = ctx->twi;
     ctx->keys.bkw = ctx->bkw;
     ctx->keys.bkc = ctx->bkc;
+    ctx->keys.bkn = ctx->bkn;
     ctx->keys.roots = ctx->roots;
     *out = ctx;
     return FHE_OK;
@@ -299,7 +302,7 @@ extern "C" void fhe_ctx_destroy(fhe_ctx* ctx) {
             for (hipEvent_t ev : tl.ev) ctx->event_pool.push_back(ev);
         for (hipEvent_t ev : ctx->event_pool) (void)hipEventDestroy(ev);
         for (void* p : {(void*)ctx->bkd, (void*)ctx->ksb, (void*)ctx->twf,
-                        (void*)ctx->twi, (void*)ctx->big, (void*)ctx->bkw, (void*)ctx->bkc, (void*)ctx->roots})
+                        (void*)ctx->twi, (void*)ctx->big, (void*)ctx->bkw, (void*)ctx->bkc, (void*)ctx->bkn, (void*)ctx->roots})
             if (p) (void)hipFree(p);
         if (ctx->stream) (void)hipStreamDestroy(ctx->stream);
         if (ctx->order) (void)hipEventDestroy(ctx->order);
@@ -440,16 +443,16 @@ extern "C" int fhe_debug_cmux(int device, int arith, const uint32_t* bk_i, int32
     make_roots(roots);
     uint64_t *d_twf = nullptr, *d_twi = nullptr, *d_bkd = nullptr;
     uint32_t *d_bk = nullptr, *d_acc = nullptr;
-    dev::fft::cd *d_roots = nullptr, *d_bkw = nullptr;
+    dev::fft::cd *d_roots = nullptr, *d_bkn = nullptr;
     const size_t bk_words = 4 * 2 * kN, bkd_words = 2 * 32 * 2 * 64;
-    const size_t roots_bytes = roots.size() * sizeof(dev::fft::cd), bkw_bytes = dev::kKeyStep * sizeof(dev::fft::cd);
+    const size_t roots_bytes = roots.size() * sizeof(dev::fft::cd), bkn_bytes = dev::kKeyStep * sizeof(dev::fft::cd);
     hipError_t e = hipSuccess;
     auto step = [&](hipError_t r) { if (e == hipSuccess) e = r; };
     step(hipMalloc((void**)&d_twf, 8192));
     step(hipMalloc((void**)&d_twi, 8192));
     step(hipMalloc((void**)&d_bkd, bkd_words * 8));
     step(hipMalloc((void**)&d_roots, roots_bytes));
-    step(hipMalloc((void**)&d_bkw, bkw_bytes));
+    step(hipMalloc((void**)&d_bkn, bkn_bytes));
     step(hipMalloc((void**)&d_bk, bk_words * 4));
     step(hipMalloc((void**)&d_acc, 2 * kN * 4));
     if (e == hipSuccess) {
@@ -461,16 +464,16 @@ extern "C" int fhe_debug_cmux(int device, int arith, const uint32_t* bk_i, int32
     }
     if (e == hipSuccess)
         step(arith == 0 ? dev::launch_bk_prepare(d_bk, d_bkd, d_twf, 1, nullptr)
-                        : dev::launch_bk_prepare_fft(d_bk, d_bkw, nullptr, d_roots, 1, nullptr));
+                        : dev::launch_bk_prepare_fft(d_bk, nullptr, nullptr, d_bkn, d_roots, 1, nullptr));
     dev::DeviceKeys K{};
     K.twf = d_twf;
     K.twi = d_twi;
-    K.bkw = d_bkw;
+    K.bkn = d_bkn;
     K.roots = d_roots;
     if (e == hipSuccess) step(dev::launch_debug_cmux(K, arith, d_bkd, abar, d_acc, nullptr));
     if (e == hipSuccess) step(hipDeviceSynchronize());
     if (e == hipSuccess) step(hipMemcpy(acc, d_acc, 2 * kN * 4, hipMemcpyDeviceToHost));
-    for (void* p : {(void*)d_twf, (void*)d_twi, (void*)d_bkd, (void*)d_roots, (void*)d_bkw, (void*)d_bk, (void*)d_acc})
+    for (void* p : {(void*)d_twf, (void*)d_twi, (void*)d_bkd, (void*)d_roots, (void*)d_bkn, (void*)d_bk, (void*)d_acc})
         if (p) (void)hipFree(p);
     return e == hipSuccess ? FHE_OK : hip_fail(e, "fhe_debug_cmux");
 }

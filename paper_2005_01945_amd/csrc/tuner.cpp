@@ -44,10 +44,11 @@ int tune_bucket(size_t width) {
     return b;
 }
 
-// Before any measurement: FFT arithmetic everywhere; four waves per gate up to
-// one gate per CU, two waves per gate up to two, groups of four gates beyond.
-// Measured blind rotations (ms) at 256 / 512 / 1,024 gates on 256 CUs: four
-// waves 2.2 / 4.4 / 8.8, two waves 2.7 / 3.0 / 6.0, groups 4.8 / 4.8 / 4.8.
+// Before any measurement: FFT arithmetic everywhere; eight waves per gate (the
+// shape named four) up to one gate per CU, two waves per gate up to two, groups
+// of four gates beyond.  Measured blind rotations (ms) at 256 / 512 / 1,024
+// gates on 256 CUs: eight waves 1.9 / 3.4 / 6.9, two waves 2.7 / 3.2 / 6.3,
+// groups 4.5 / 4.5 / 4.5.
 static dev::LaunchConfig default_shape(const fhe_ctx* ctx, size_t width) {
     const size_t cus = (size_t)ctx->cu_count;
     if (width <= cus) return dev::LaunchConfig{4, 1, 1};
