@@ -160,7 +160,7 @@ int fhe_phase(const fhe_secret_key* sk, const uint32_t* ct, size_t count, int32_
 /* ---------------------------------------------------------------------- */
 
 /* Uploads the cloud key to HIP device `device`, converts the bootstrapping
- * key for both arithmetics (the FFT domain, the default, in three layouts of
+ * key for both arithmetics (the FFT domain, the default, in two layouts of
  * 65.5 MB, and the NTT domain over p = 2^64 - 2^32 + 1, 32.8 MB) and lays out
  * the key-switching key as byte limbs in matrix-operand order (50.3 MB).  The cloud key may be freed
  * afterwards.  Errors: FHE_EDEVICE if the device is missing or not gfx950;
@@ -358,11 +358,12 @@ int fhe_ctx_set_graphs(fhe_ctx* ctx, int enable);
 /*     gate (throughput shape); arith 0: that many ciphertexts per          */
 /*     workgroup; arith 1: always groups of four ciphertexts that share     */
 /*     their key loads;                                                     */
-/*   waves_per_gate = 2, gates_per_group = 1: two wavefronts split every    */
-/*     CMux of one gate (latency shape for levels narrower than the chip);  */
+/*   waves_per_gate = 2, gates_per_group = 1: latency shape for levels       */
+/*     narrower than the chip (arith 0: two wavefronts split every CMux of  */
+/*     one gate; arith 1: eight, two gates per compute unit);               */
 /*   each of these with either arithmetic (arith 0 or 1);                   */
-/*   waves_per_gate = 4, gates_per_group = 1, arith = 1: the lowest latency, */
-/*     two wavefronts per digit row of a gate.                              */
+/*   waves_per_gate = 4, gates_per_group = 1, arith = 1: the lowest latency */
+/*     (eight wavefronts per gate, one gate per compute unit).              */
 /* The shape changes only the schedule and the exact arithmetic used to     */
 /* reach the result: every shape computes the same words.  Captured level   */
 /* schedules are recaptured after a change.                                 */

@@ -139,24 +139,6 @@ __device__ __forceinline__ void forward_root(cd (&x)[R]) {
     });
 }
 
-// Forward on R registers below a lane's own root, the butterflies of stored
-// twiddle F (see forward_lane) only.
-template <int R, int F>
-__device__ __forceinline__ void forward_lane_part(cd (&x)[R], const cd& t) {
-    constexpr int l = F == 0 ? 0 : 32 - __builtin_clz((unsigned)F), m = R >> (l + 1);
-    constexpr int d = F < 2 ? 0 : F - (1 << (l - 1));
-    unroll<0, (l == 0 ? 1 : 2)>([&](auto s_) {
-        constexpr int c = 2 * d + decltype(s_)::value;
-        unroll<0, m>([&](auto j_) {
-            constexpr int j = decltype(j_)::value;
-            if constexpr (decltype(s_)::value == 0)
-                butterfly(x[2 * m * c + j], x[2 * m * c + j + m], t.x, t.y);
-            else
-                butterfly(x[2 * m * c + j], x[2 * m * c + j + m], -t.y, t.x);
-        });
-    });
-}
-
 // Forward on R registers below a lane's own root; w[2^(l-1) + (c >> 1)] (w[0]
 // at level 0) is the twiddle of node c of level l, even c.
 template <int R, class W>
@@ -193,26 +175,6 @@ __device__ __forceinline__ void inverse_root(cd (&x)[R]) {
             butterfly_c<-32 * j / h>(x[u], x[u + h]);
         });
     });
-}
-
-// The same one level group up: the lane's lower output bits shift its
-// twiddles.  w[0] at span 1, w[1] at span 2, w[2], w[3] at span 4 (R = 8); the
-// second half of a span's twiddles is -i times the first.
-template <class W>
-__device__ __forceinline__ void inverse_lane8(cd (&x)[8], const W& w) {
-    unroll<0, 4>([&](auto k_) {
-        constexpr int k = decltype(k_)::value;
-        butterfly(x[2 * k], x[2 * k + 1], w[0].x, w[0].y);
-    });
-    unroll<0, 2>([&](auto k_) {
-        constexpr int k = 4 * decltype(k_)::value;
-        butterfly(x[k], x[k + 2], w[1].x, w[1].y);
-        butterfly(x[k + 1], x[k + 3], w[1].y, -w[1].x);
-    });
-    butterfly(x[0], x[4], w[2].x, w[2].y);
-    butterfly(x[1], x[5], w[3].x, w[3].y);
-    butterfly(x[2], x[6], w[2].y, -w[2].x);
-    butterfly(x[3], x[7], w[3].y, -w[3].x);
 }
 
 // Nearest integer of v (|v| < 2^50) mod 2^32: adding 1.5 * 2^52 leaves the

@@ -54,10 +54,8 @@ struct DeviceKeys {
     const uint8_t* ksb;       // KSK rows v = 1..3 as byte limbs in matrix-operand order (50 MB)
     const uint64_t* twf;      // forward twiddles [32][32]
     const uint64_t* twi;      // inverse twiddles (with N^-1) [32][32]
-    // FFT products: BK halves at the leaves in the layouts of the kernels with
-    // two waves per gate, groups and eight waves per gate (65.5 MB each) and
-    // the roots E(k) = exp(i pi k / 1024), k < 2048.
-    const fft::cd* bkw;
+    // FFT products: BK halves at the leaves in the layouts of the group kernel
+    // and of the kernel with eight waves per gate (65.5 MB each), and the roots E(k) = exp(i pi k / 1024), k < 2048.
     const fft::cd* bkc;
     const fft::cd* bkn;
     const fft::cd* roots;
@@ -70,8 +68,8 @@ constexpr int kKeyStep = 4 * 4 * 512;
 // BK (uint32 [n][2l][2][N], device) -> NTT-domain kernel layout.
 hipError_t launch_bk_prepare(const uint32_t* bk, uint64_t* bkd, const uint64_t* twf,
                              uint32_t n_lwe, hipStream_t s);
-// The same to the FFT domain (any layout may be null).
-hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc, fft::cd* bkn, const fft::cd* roots,
+// The same to the FFT domain (either layout may be null).
+hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkc, fft::cd* bkn, const fft::cd* roots,
                                  uint32_t n_lwe, hipStream_t s);
 
 // Kernel shape of a blind-rotation launch.  arith: 0 = NTT over the Goldilocks
@@ -80,8 +78,8 @@ hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc,
 //     {1, 2, 4, 8} gates share a workgroup (and its twiddle copy in LDS);
 //     waves_per_gate = 2: two waves split each CMux of one gate.
 //   arith 1: waves_per_gate = 1: groups of four gates on four waves, whatever
-//     gates_per_group; waves_per_gate = 2: two waves per gate; waves_per_gate =
-//     4: the lowest-latency shape, eight waves per gate, two per digit row.
+//     gates_per_group; waves_per_gate = 2 and 4: eight waves per gate, two per
+//     digit row, laid out for two gates per compute unit (2) or one (4).
 // Every shape gives the same words.
 struct LaunchConfig {
     uint32_t waves_per_gate;

@@ -361,18 +361,17 @@ __device__ __forceinline__ void cmux_step(WaveLds& W, int ai, const uint64_t* __
 
 using fft::cd;
 
-// Leaf and coefficient order of a transform on one wavefront (64 lanes x 8
-// registers, 512 = 8 x 8 x 8): coefficient j = lane + 64 reg before, leaf
+// The key's transform, on one wavefront (64 lanes x 8 registers, 512 = 8 x 8 x
+// 8): coefficient j = lane + 64 reg before, leaf
 // p = 8 lane + reg after.  Between the passes the registers are exchanged with
 // the lanes' upper, then lower three bits through the wave's own 9 KB of LDS;
 // the strides of 72 and 9 sixteen-byte slots spread the sixteen lanes that
 // read together over all 64 banks.
 constexpr int kExSlots = 576;
 
-// A lane's twiddles, held in registers across the rotation.
+// A lane's twiddles of passes 2 and 3.
 struct LaneTwiddles {
-    cd f2[4], f3[4];  // forward passes 2 and 3
-    cd i2[4], i1[4];  // inverse passes 2 and 1 (conjugates)
+    cd f2[4], f3[4];
 };
 
 __device__ __forceinline__ cd conj_root(const cd* __restrict__ roots, int k) {
@@ -387,14 +386,6 @@ __device__ __forceinline__ void load_forward_twiddles(LaneTwiddles& W, const cd*
     const int n3 = 4 + 16 * brv3(lane >> 3) + 128 * brv3(lane & 7);
     W.f2[0] = roots[n2], W.f2[1] = roots[n2 / 2], W.f2[2] = roots[n2 / 4], W.f2[3] = roots[n2 / 4 + 256];
     W.f3[0] = roots[n3], W.f3[1] = roots[n3 / 2], W.f3[2] = roots[n3 / 4], W.f3[3] = roots[n3 / 4 + 256];
-}
-
-__device__ __forceinline__ void load_inverse_twiddles(LaneTwiddles& W, const cd* __restrict__ roots, int lane) {
-    const int m0 = lane & 7;
-    W.i2[0] = conj_root(roots, 128 * m0), W.i2[1] = conj_root(roots, 64 * m0);
-    W.i2[2] = conj_root(roots, 32 * m0), W.i2[3] = conj_root(roots, 32 * m0 + 256);
-    W.i1[0] = conj_root(roots, 16 * lane), W.i1[1] = conj_root(roots, 8 * lane);
-    W.i1[2] = conj_root(roots, 4 * lane), W.i1[3] = conj_root(roots, 4 * lane + 256);
 }
 
 // Exchanges through the wave's slots: registers written at base + stride k,
@@ -418,28 +409,6 @@ __device__ __forceinline__ void fft512_forward(cd (&x)[8], cd* ex, const LaneTwi
     fft::forward_lane<8>(x, [&](auto k) { return W.f3[decltype(k)::value]; });
 }
 
-// Inverse of the above without the factor 1/512, which the key carries, and
-// without the twist (finish_words applies it).
-__device__ __forceinline__ void fft512_inverse(cd (&x)[8], cd* ex, const LaneTwiddles& W, int lane) {
-    const int hi = lane >> 3, lo = lane & 7;
-    fft::inverse_root<8>(x);
-    wave_exchange<1, 9>(x, ex + hi * 72 + 9 * lo, ex + hi * 72 + lo);
-    fft::inverse_lane8(x, W.i2);
-    wave_exchange<8, 72>(x, ex + hi * 72 + lo, ex + lane);
-    fft::inverse_lane8(x, W.i1);
-}
-
-// Twist (tw: LDS table of the 512 factors) and rounding: word e (0..15) of
-// coefficient lane + 64 e.
-__device__ __forceinline__ void finish_words(const cd (&x)[8], const cd* tw, int lane, uint32_t (&v)[16]) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const cd t = tw[64 * q + lane];
-        v[q] = fft::round_word(__builtin_fma(t.x, x[q].x, -(t.y * x[q].y)));
-        v[q + 8] = fft::round_word(__builtin_fma(t.x, x[q].y, t.y * x[q].x));
-    }
-}
-
 // D = X^ai ACC - ACC plus the rounding offset of both digits, of coefficient
 // m with d4 = 4 (m - ai) (see rotated_word), with the top bit of each digit's
 // field flipped so that the signed 10-bit fields at 22 and 12 are the digits.
@@ -447,32 +416,6 @@ __device__ __forceinline__ uint32_t digit_word(uint32_t v, uint32_t own, int d4)
     uint32_t sgn;  // (the optimiser would turn the bit-field extract into a compare and a select)
     asm("v_bfe_i32 %0, %1, 12, 1" : "=v"(sgn) : "v"(d4));
     return (((v + sgn) ^ sgn) + (kDecompOffset - own)) ^ 0x80200000u;
-}
-
-// Both digit rows of polynomial a: coefficient lane + 64 e, e < 8 real, else
-// imaginary part of register e mod 8.
-__device__ __forceinline__ void wave_digits(const uint32_t* a, int ai, int lane, cd (&x)[2][8]) {
-    const lds_u32* am = lds_column(a, lane);
-    const uint32_t abase = (uint32_t)(uintptr_t)(const lds_u32*)a;
-    const int d4 = 4 * (lane - ai);
-    uint32_t v[16], own[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        v[e] = rotated_word(abase, d4 + 256 * e);
-        own[e] = am[64 * e];
-    }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const uint32_t z = digit_word(v[e], own[e], d4 + 256 * e);
-#pragma unroll
-        for (int d = 0; d < 2; ++d) {
-            const double dg = (double)(int32_t)__builtin_amdgcn_sbfe((int32_t)z, 22 - 10 * d, 10);
-            if (e < 8)
-                x[d][e & 7].x = dg;
-            else
-                x[d][e & 7].y = dg;
-        }
-    }
 }
 
 __device__ __forceinline__ void mac(cd& o, const cd& k, const cd& x) {
@@ -492,93 +435,41 @@ __device__ __forceinline__ void lds_add(uint32_t* p, uint32_t v) {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// LDS of a gate on two wavefronts: accumulator, each wave's exchange slots, the
-// twist factors and the digit spectra that the waves share.
-struct alignas(4096) PairFftLds {
-    uint32_t acc[2][1024];
-    cd ex[2][kExSlots];
-    cd tw[512];
-    cd spec[4][512];
-};
-
-// Key word of row r, output o, register j, lane (wave layout).
-__device__ __forceinline__ const cd* key_row(const cd* __restrict__ key, int r, int o, int lane) {
-    return key + ((r * 4 + o) * 8) * 64 + lane;
-}
-
-__device__ __forceinline__ void load_key_row(cd (&k)[8], const cd* __restrict__ key, int r, int o, int lane) {
-    const cd* p = key_row(key, r, o, lane);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) k[j] = p[64 * j];
-}
-
-// One CMux step of a gate on two wavefronts.  Wave w transforms rows 2 w and
-// 2 w + 1 (both digits of polynomial w) and finishes outputs 2 w and 2 w + 1
-// (both halves of column w); the rows' spectra meet in LDS.  Two barriers per
-// step: spectra written, ACC updated.
-__device__ __forceinline__ void pair_step(PairFftLds& S, int ai, const cd* __restrict__ key, const LaneTwiddles& T,
-                                          int wave, int lane) {
-    cd* ex = S.ex[wave];
-    cd pre[2][2][8];  // keys of rows 0 and 1, on their way during the transforms
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int r = 0; r < 2; ++r) load_key_row(pre[k][r], key, r, 2 * wave + k, lane);
-    sched_fence();
-    cd x[2][8];
-    wave_digits(S.acc[wave], ai, lane, x);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        fft512_forward(x[k], ex, T, lane);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) S.spec[2 * wave + k][64 * j + lane] = x[k][j];
-    }
-    lds_barrier();  // spectra written; both waves have read ACC
-    cd out[2][8];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const cd v = S.spec[r][64 * j + lane];
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                if (r == 0) out[k][j] = {0.0, 0.0};
-                mac(out[k][j], r < 2 ? pre[k][r & 1][j] : key_row(key, r, 2 * wave + k, lane)[64 * j], v);
-            }
-        }
-    }
-    uint32_t lo[16], hi[16];
-    fft512_inverse(out[0], ex, T, lane);
-    finish_words(out[0], S.tw, lane, lo);
-    fft512_inverse(out[1], ex, T, lane);
-    finish_words(out[1], S.tw, lane, hi);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) lds_add(&S.acc[wave][lane + 64 * e], lo[e] + (hi[e] << 16));
-    lds_barrier();  // ACC updated; spectra free
-}
-
 // ---------------------------------------------------------------------------
 // One gate on eight wavefronts, two per digit row (and per output): wave
 // (row, half) keeps the half of the ring X^512 - i = (X^256 - w)(X^256 + w),
 // w = E(256), i.e. 256 of a row's leaves, four registers per lane.  The four
 // waves of a polynomial share its digit words; both waves of a row fold its
 // digits by the first split, and the other eight levels are four passes of two
-// levels in registers.  Registers and lane
-// bits are exchanged between the passes: bits 5, 4 by v_permlane32/16_swap,
-// bits 3, 2 and bits 1, 0 through the wave's slots in LDS.  The last level of
-// the inverse joins the two halves through LDS.
+// levels in registers.  Registers and lane bits are exchanged between the
+// passes: bits 5, 4 by v_permlane32/16_swap, bits 3, 2 by moves within rows of
+// 16 lanes, bits 1, 0 through the wave's slots in LDS.  The last level of the
+// inverse joins the two halves through LDS.
 // ---------------------------------------------------------------------------
 
 constexpr int kNarrowSlots = 320;
 constexpr int kPad = 64;  // words before each accumulator polynomial: -ACC[960 + k]
 
+// LEAN: two gates per compute unit, in half of the LDS and 128 registers.  The
+// spectra stay in the waves' exchange slots (one more barrier), the twiddles of
+// passes 3 and 4 in LDS, and two rows of keys instead of four in registers.
+template <bool LEAN>
 struct alignas(16) NarrowLds {
     uint32_t acc[2][kPad + 1024];
     uint32_t tail[kPad];  // (makes the padded view below end inside the struct)
     uint4 digits[2][4][64];  // digit words of coefficients lane + 64 (4 part + word)
     cd ex[8][kNarrowSlots];
-    cd spec[4][2][256];
-    cd tw[2][256];  // [half]: E(-j), E(-5 j)
+    cd spec[LEAN ? 1 : 8][LEAN ? 1 : 256];
+    cd tw[2][256];                       // [half]: E(-j), E(-5 j)
+    cd fwd[LEAN ? 2 : 1][LEAN ? 4 : 1][64];  // [half]: f3, f4 of NarrowTwiddles
+    cd inv[LEAN ? 4 : 1][64];                // i3, i4
+    // The spectrum of a wave, 256 leaves.
+    __device__ __forceinline__ cd* spectrum(int wave) {
+        if constexpr (LEAN)
+            return ex[wave];
+        else
+            return spec[wave];
+    }
     // The accumulator polynomials behind their pads.
     __device__ __forceinline__ uint32_t (&view())[2][kPad + 1024] {
         return *reinterpret_cast<uint32_t (*)[2][kPad + 1024]>(&acc[0][kPad]);
@@ -591,8 +482,9 @@ struct NarrowTwiddles {
     cd i2[2], i3[2], i4[2];       // inverse passes 2..4 (conjugates)
 };
 
-__device__ __forceinline__ void load_narrow_twiddles(NarrowTwiddles& T, const cd* __restrict__ roots, int half,
-                                                     int lane) {
+template <bool LEAN>
+__device__ __forceinline__ void load_narrow_twiddles(NarrowLds<LEAN>& S, NarrowTwiddles& T,
+                                                     const cd* __restrict__ roots, int wave, int half, int lane) {
     const int p2 = half + 2 * ((lane >> 5) & 1) + 4 * ((lane >> 4) & 1);
     const int p3 = p2 + 8 * ((lane >> 3) & 1) + 16 * ((lane >> 2) & 1);
     const int p4 = p3 + 32 * ((lane >> 1) & 1) + 64 * (lane & 1);
@@ -603,6 +495,16 @@ __device__ __forceinline__ void load_narrow_twiddles(NarrowTwiddles& T, const cd
     T.i2[0] = conj_root(roots, 256 * (lane & 3)), T.i2[1] = conj_root(roots, 128 * (lane & 3));
     T.i3[0] = conj_root(roots, 64 * (lane & 15)), T.i3[1] = conj_root(roots, 32 * (lane & 15));
     T.i4[0] = conj_root(roots, 16 * lane), T.i4[1] = conj_root(roots, 8 * lane);
+    if constexpr (LEAN) {
+        if (wave < 2) {
+            S.fwd[half][0][lane] = T.f3[0], S.fwd[half][1][lane] = T.f3[1];
+            S.fwd[half][2][lane] = T.f4[0], S.fwd[half][3][lane] = T.f4[1];
+            S.inv[0][lane] = T.i3[0], S.inv[1][lane] = T.i3[1];
+            S.inv[2][lane] = T.i4[0], S.inv[3][lane] = T.i4[1];
+        }
+    }
+    for (int j = lane; j < 256; j += 64)
+        if (wave < 2) S.tw[half][j] = conj_root(roots, half ? 5 * j : j);
 }
 
 __device__ __forceinline__ double with_words(uint32_t lo, uint32_t hi) {
@@ -637,6 +539,36 @@ __device__ __forceinline__ void exchange_high(cd (&x)[4]) {
     for (int k = 0; k < 4; k += 2) {
         lane_swap<true>(x[k].x, x[k + 1].x);
         lane_swap<true>(x[k].y, x[k + 1].y);
+    }
+}
+
+// The same with lane bit 3 (N = 8) or 2 (N = 4), by moves within rows of 16.
+template <int N>
+__device__ __forceinline__ void row_swap(double& a, double& b) {
+    constexpr int kUpper = N == 8 ? 0xC : 0xA;  // banks of four lanes that have the bit
+    uint32_t x[2] = {(uint32_t)__builtin_bit_cast(uint64_t, a), (uint32_t)(__builtin_bit_cast(uint64_t, a) >> 32)};
+    uint32_t y[2] = {(uint32_t)__builtin_bit_cast(uint64_t, b), (uint32_t)(__builtin_bit_cast(uint64_t, b) >> 32)};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const uint32_t old = x[k];
+        x[k] = (uint32_t)__builtin_amdgcn_update_dpp((int)x[k], (int)y[k], 0x110 + N, 0xF, kUpper, false);
+        y[k] = (uint32_t)__builtin_amdgcn_update_dpp((int)y[k], (int)old, 0x100 + N, 0xF, 0xF ^ kUpper, false);
+    }
+    a = with_words(x[0], x[1]);
+    b = with_words(y[0], y[1]);
+}
+
+// Register bits (1, 0) <-> lane bits (3, 2).
+__device__ __forceinline__ void exchange_mid(cd (&x)[4]) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        row_swap<8>(x[k].x, x[k + 2].x);
+        row_swap<8>(x[k].y, x[k + 2].y);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k += 2) {
+        row_swap<4>(x[k].x, x[k + 1].x);
+        row_swap<4>(x[k].y, x[k + 1].y);
     }
 }
 
@@ -676,17 +608,17 @@ __device__ __forceinline__ void load_narrow_keys(cd (&k)[4], const cd* __restric
 
 // One CMux step of wave (row, half).  ka[k]: the step's keys of row (row + k)
 // mod 4; k = 0, 1 are loaded a step ahead (from `next`), k = 2, 3 during the
-// forward transform.  Four barriers: digits written, spectra written, halves
-// joined, ACC updated.
-__device__ __forceinline__ void narrow_step(NarrowLds& S, int ai, const cd* __restrict__ cur,
-                                            const cd* __restrict__ next, cd (&ka)[4][4], const NarrowTwiddles& T,
-                                            int row, int half, int lane) {
+// forward transform (LEAN: into the registers of 0 and 1 once those are used).
+// Four barriers: digits written, spectra written, halves joined, ACC updated
+// (LEAN: one more, spectra read).
+template <bool LEAN>
+__device__ __forceinline__ void narrow_step(NarrowLds<LEAN>& S, int ai, const cd* __restrict__ cur,
+                                            const cd* __restrict__ next, cd (&ka)[LEAN ? 2 : 4][4],
+                                            const NarrowTwiddles& T, int row, int half, int lane) {
     cd* ex = S.ex[2 * row + half];
-    const int u = lane >> 2, v = lane & 3, h4 = lane >> 4;
-    cd* e2a = ex + 80 * h4 + (lane & 15);                  // bits 3, 2: stride 20 by register,
-    cd* e2b = ex + 80 * h4 + 20 * (u & 3) + v;             // stride 4 after the exchange
-    cd* e3a = ex + 20 * u + v;                             // bits 1, 0: stride 5,
-    cd* e3b = ex + 20 * u + 5 * v;                         // stride 1
+    const int u = lane >> 2, v = lane & 3;
+    cd* e3a = ex + 20 * u + v;      // bits 1, 0: stride 5 by register,
+    cd* e3b = ex + 20 * u + 5 * v;  // stride 1 after the exchange
     cd x[4];
     {
         // D = X^ai ACC - ACC, four words per lane and wave: the four waves of
@@ -731,28 +663,62 @@ __device__ __forceinline__ void narrow_step(NarrowLds& S, int ai, const cd* __re
             x[k].y = __builtin_fma(c, (double)(d[k + 4] + d[k + 12]), (double)d[k + 8]);
         }
     }
-    load_narrow_keys(ka[2], cur, (row + 2) & 3, row, half, lane);
+    if constexpr (!LEAN) load_narrow_keys(ka[2], cur, (row + 2) & 3, row, half, lane);
     sched_fence();
     forward4(x, T.f1);
     exchange_high(x);
     forward4(x, T.f2);
-    exchange_low<20, 4>(x, e2a, e2b);
-    load_narrow_keys(ka[3], cur, (row + 3) & 3, row, half, lane);
-    sched_fence();
-    forward4(x, T.f3);
-    exchange_low<5, 1>(x, e3a, e3b);
-    forward4(x, T.f4);
+    exchange_mid(x);
+    if constexpr (LEAN) {
+        const cd w3[2] = {S.fwd[half][0][lane], S.fwd[half][1][lane]};
+        forward4(x, w3);
+        exchange_low<5, 1>(x, e3a, e3b);
+        const cd w4[2] = {S.fwd[half][2][lane], S.fwd[half][3][lane]};
+        forward4(x, w4);
+    } else {
+        load_narrow_keys(ka[3], cur, (row + 3) & 3, row, half, lane);
+        sched_fence();
+        forward4(x, T.f3);
+        exchange_low<5, 1>(x, e3a, e3b);
+        forward4(x, T.f4);
+    }
+    cd* mine = S.spectrum(2 * row + half);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) S.spec[row][half][64 * j + lane] = x[j];
+    for (int j = 0; j < 4; ++j) mine[64 * j + lane] = x[j];
     lds_barrier();  // spectra written
     cd out[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    auto mac_row = [&](int k, const cd (&keys)[4], const cd (&s)[4]) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (k == 0) out[j] = {0.0, 0.0};
-            mac(out[j], ka[k][j], k == 0 ? x[j] : S.spec[(row + k) & 3][half][64 * j + lane]);
+            mac(out[j], keys[j], s[j]);
         }
+    };
+    auto read_row = [&](int k, cd (&s)[4]) {
+        const cd* p = S.spectrum(2 * ((row + k) & 3) + half);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] = p[64 * j + lane];
+    };
+    mac_row(0, ka[0], x);
+    if constexpr (LEAN) {
+        cd s1[4], s2[4], s3[4];
+        load_narrow_keys(ka[0], cur, (row + 2) & 3, row, half, lane);
+        read_row(1, s1);
+        mac_row(1, ka[1], s1);
+        load_narrow_keys(ka[1], cur, (row + 3) & 3, row, half, lane);
+        read_row(2, s2);
+        read_row(3, s3);
+        lds_barrier();  // spectra read
+        mac_row(2, ka[0], s2);
+        mac_row(3, ka[1], s3);
+    } else {
+        cd s1[4], s2[4], s3[4];
+        read_row(1, s1);
+        read_row(2, s2);
+        read_row(3, s3);
+        mac_row(1, ka[1], s1);
+        mac_row(2, ka[2], s2);
+        mac_row(3, ka[3], s3);
     }
     sched_fence();
     fft::inverse_root<4>(out);
@@ -760,10 +726,18 @@ __device__ __forceinline__ void narrow_step(NarrowLds& S, int ai, const cd* __re
     load_narrow_keys(ka[0], next, (row + 0) & 3, row, half, lane);
     sched_fence();
     inverse4(out, T.i2);
-    exchange_low<4, 20>(out, e2b, e2a);
-    inverse4(out, T.i3);
-    exchange_high(out);
-    inverse4(out, T.i4);
+    exchange_mid(out);
+    if constexpr (LEAN) {
+        const cd w3[2] = {S.inv[0][lane], S.inv[1][lane]};
+        inverse4(out, w3);
+        exchange_high(out);
+        const cd w4[2] = {S.inv[2][lane], S.inv[3][lane]};
+        inverse4(out, w4);
+    } else {
+        inverse4(out, T.i3);
+        exchange_high(out);
+        inverse4(out, T.i4);
+    }
     load_narrow_keys(ka[1], next, (row + 1) & 3, row, half, lane);
     sched_fence();
     // last level and twist: with e = E(-j) even_j and o = E(-5 j) odd_j, the
@@ -1141,63 +1115,30 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     gate_epilogue<128>(io, g, S.acc, big, threadIdx.x);
 }
 
-// Blind rotation with FFT products on two wavefronts per gate, for batches of
-// one to two gates per compute unit.  Bound by latency, of the LDS exchanges
-// and of the key loads of rows 2 and 3 (registers hold those of two rows):
-// 512 gates in 3.2 ms, 256 in 2.7 ms (the integer NTTs modulo two primes that
-// this replaces: 4.6 and 4.4 ms).  Loading all four rows at the start of the
-// step needs 128 accumulation registers and as many moves: 3.3 ms at 512.
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 2)))
-void k_blind_rotate_fft_pair(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
-    __shared__ PairFftLds S;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63, h = lane >> 5, t = lane & 31;
-    const uint32_t g = blockIdx.x;
-    if (g >= count) return;  // uniform over the block
-    for (int k = threadIdx.x; k < 512; k += 128) S.tw[k] = conj_root(K.roots, k);
-    LaneTwiddles T;
-    load_forward_twiddles(T, K.roots, lane);
-    load_inverse_twiddles(T, K.roots, lane);
-    uint32_t ab[8];
-    const int bbar = gate_prologue(io, g, lane, ab);
-    if (wave == 0) acc_init(S.acc, bbar, h, t, io.tv, gate_mu(io, g));
-    const cd* key = K.bkw;
-    __syncthreads();
-#pragma unroll 1
-    for (int i = 0; i < NLWE; ++i) {
-        const int ai = __builtin_amdgcn_readlane(ab[0], i & 63);
-        pair_step(S, ai, key, T, wave, lane);
-        key += kKeyStep;
-        if ((i & 63) == 63) {
-#pragma unroll
-            for (int r = 0; r < 7; ++r) ab[r] = ab[r + 1];
-        }
-    }
-    gate_epilogue<128>(io, g, S.acc, big, threadIdx.x);
-}
-
-// Blind rotation with FFT products on eight wavefronts per gate, for the
-// lowest latency: one gate in 1.65 ms, 256 in 1.9 ms.  A step's 7,900 cycles
-// are a chain of ten LDS round trips and four barriers around 430 VALU per
-// wave; two waves per SIMD fill each other's gaps (four wavefronts per gate,
-// one per row, with the same arithmetic: 2.06 and 2.24 ms; the integer NTTs
-// modulo two primes before that: 3.2 and 3.3 ms).  The 128 KB of key per step
-// are 2,000 cycles of the vector memory path, so the loads are spread over the
-// step: all in one place they delayed it to 2.0 ms.
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// Blind rotation with FFT products on eight wavefronts per gate, for batches
+// that leave compute units with one gate (LEAN = false: one gate 1.40 ms, 256
+// gates 1.71 ms) or two (LEAN: 512 gates 2.86 ms, 300 gates 2.60).  A step of
+// one gate takes 6,700 cycles, a chain of LDS round trips and four barriers
+// around 430 VALU per wave; two waves per SIMD fill each other's gaps.  With
+// two gates LDS is busy 70% of the time, most of it writes (64 B per clock).
+// Both exchanges of lane bits 3 to 0 through LDS: 1.53 and 3.08 ms (bits 1 and
+// 0 by moves as well, which need selects: 1.46 and 2.96).  The 128 KB of key
+// per step and gate are 2,000 cycles of the vector memory path, so the loads
+// are spread over the step: all in one place they cost 0.3 ms.  Four wavefronts
+// per gate, one per row: 2.06 and 4.2 ms; two: 2.54 and 3.3.  The integer NTTs
+// modulo two primes that these replace: 3.2 ms (one gate) and 4.6 (512).
+template <bool LEAN>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(LEAN ? 4 : 2, LEAN ? 4 : 2)))
 void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
-    __shared__ NarrowLds S;
+    __shared__ NarrowLds<LEAN> S;
+    static_assert(!LEAN || 2 * sizeof(NarrowLds<LEAN>) <= 160 * 1024, "two gates per compute unit");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = wave >> 1, half = wave & 1;
     const int lane = threadIdx.x & 63, h = lane >> 5, t = lane & 31;
     const uint32_t g = blockIdx.x;
     if (g >= count) return;  // uniform over the block
-    {
-        const int hf = threadIdx.x >> 8, j = threadIdx.x & 255;
-        S.tw[hf][j] = conj_root(K.roots, hf ? 5 * j : j);
-    }
     NarrowTwiddles T;
-    load_narrow_twiddles(T, K.roots, half, lane);
+    load_narrow_twiddles(S, T, K.roots, wave, half, lane);
     uint32_t ab[8];
     const int bbar = gate_prologue(io, g, lane, ab);
     uint32_t (&acc)[2][kPad + 1024] = S.view();
@@ -1208,9 +1149,9 @@ void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, 
         for (int p = 0; p < 2; ++p) S.acc[p][lane] = 0u - acc[p][960 + lane];
     }
     const cd* key = K.bkn;
-    cd ka[4][4];
+    cd ka[LEAN ? 2 : 4][4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) load_narrow_keys(ka[k], key, (row + k) & 3, row, half, lane);
+    for (int k = 0; k < 2; ++k) load_narrow_keys(ka[k], key, (row + k) & 3, row, half, lane);
     __syncthreads();
 #pragma unroll 1
     for (int b = 0; b < NLWE; b += 64) {
@@ -1459,12 +1400,12 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
 }
 
 // BK -> the FFT domain, scaled by 1/512 (the inverse transform's factor; a
-// power of two, exact), in both layouts: one wave per polynomial (CMux i, row
+// power of two, exact), in the kernels' layouts: one wave per polynomial (CMux i, row
 // r, column c) transforms its low and its high signed half words.
-//   bkw[i][r][o][reg][lane] (k_blind_rotate_fft), leaf 8 lane + reg;
+//   bkn[i][r][o][leaf / 256][leaf % 4][leaf % 256 / 4] (k_blind_rotate_narrow);
 //   bkc[i][leaf % 32][leaf / 128][16 r + 4 (leaf / 32 % 4) + o] (k_blind_rotate_group).
-__global__ __launch_bounds__(kBlockThreads) void k_bk_prepare_fft(const uint32_t* __restrict__ bk, cd* __restrict__ bkw,
-                                                                  cd* __restrict__ bkc, cd* __restrict__ bkn, const cd* __restrict__ roots,
+__global__ __launch_bounds__(kBlockThreads) void k_bk_prepare_fft(const uint32_t* __restrict__ bk, cd* __restrict__ bkc,
+                                                                  cd* __restrict__ bkn, const cd* __restrict__ roots,
                                                                   uint32_t npolys) {
     __shared__ cd ex[kWavesPerBlock][kExSlots];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1493,7 +1434,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_bk_prepare_fft(const uint32_t
             const cd v = {x[j].x * (1.0 / 512), x[j].y * (1.0 / 512)};
             const uint32_t leaf = 8 * lane + j;
             if (bkn) bkn[(size_t)i * kKeyStep + ((r * 4 + o) * 8 + 4 * (leaf / 256) + leaf % 4) * 64 + leaf % 256 / 4] = v;
-            if (bkw) bkw[(size_t)i * kKeyStep + ((r * 4 + o) * 8 + j) * 64 + lane] = v;
             if (bkc) bkc[(size_t)i * kKeyStep + ((leaf % 32) * 4 + leaf / 128) * 64 + 16 * r + 4 * (leaf / 32 % 4) + o] = v;
         }
     }
@@ -1502,16 +1442,15 @@ __global__ __launch_bounds__(kBlockThreads) void k_bk_prepare_fft(const uint32_t
 // One CMux on acc[2][N] in global memory with the FFT products (eight waves).
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_debug_cmux_fft(DeviceKeys K, int32_t abar, uint32_t* __restrict__ accg) {
-    __shared__ NarrowLds S;
+    __shared__ NarrowLds<false> S;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int row = wave >> 1, half = wave & 1;
     NarrowTwiddles T;
-    load_narrow_twiddles(T, K.roots, half, lane);
+    load_narrow_twiddles(S, T, K.roots, wave, half, lane);
     cd ka[4][4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) load_narrow_keys(ka[k], K.bkn, (row + k) & 3, row, half, lane);
+    for (int k = 0; k < 2; ++k) load_narrow_keys(ka[k], K.bkn, (row + k) & 3, row, half, lane);
     uint32_t (&acc)[2][kPad + 1024] = S.view();
-    for (int k = threadIdx.x; k < 512; k += 512) S.tw[k >> 8][k & 255] = conj_root(K.roots, k >> 8 ? 5 * (k & 255) : k);
     for (int k = threadIdx.x; k < 2 * N; k += 512) acc[k / N][k % N] = accg[k];
     for (int k = threadIdx.x; k < 2 * kPad; k += 512) S.acc[k / kPad][k % kPad] = 0u - accg[k / kPad * N + 960 + k % kPad];
     __syncthreads();
@@ -1779,8 +1718,8 @@ hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* 
     if (cfg.arith == 1) {
         switch (cfg.waves_per_gate) {
         case 1: return launch(k_blind_rotate_group, 4, 256);
-        case 2: return launch(k_blind_rotate_fft_pair, 1, 128);
-        case 4: return launch(k_blind_rotate_narrow, 1, 512);
+        case 2: return launch(k_blind_rotate_narrow<true>, 1, 512);
+        case 4: return launch(k_blind_rotate_narrow<false>, 1, 512);
         default: return hipErrorInvalidValue;
         }
     }
@@ -1840,11 +1779,11 @@ hipError_t launch_debug_cmux(const DeviceKeys& K, int arith, const uint64_t* bk_
     return hipGetLastError();
 }
 
-hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkw, fft::cd* bkc, fft::cd* bkn, const fft::cd* roots,
+hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkc, fft::cd* bkn, const fft::cd* roots,
                                  uint32_t n_lwe, hipStream_t s) {
     const uint32_t npolys = n_lwe * 8;
     const uint32_t blocks = (npolys + kWavesPerBlock - 1) / kWavesPerBlock;
-    hipLaunchKernelGGL(k_bk_prepare_fft, dim3(blocks), dim3(kBlockThreads), 0, s, bk, bkw, bkc, bkn, roots, npolys);
+    hipLaunchKernelGGL(k_bk_prepare_fft, dim3(blocks), dim3(kBlockThreads), 0, s, bk, bkc, bkn, roots, npolys);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 // Device context and gate-bootstrapping entry points.
 //
 // A context keeps the cloud key resident on one GPU: the bootstrapping key
-// converted once to the FFT domain (three layouts of 65.5 MB) and to the NTT
+// converted once to the FFT domain (two layouts of 65.5 MB) and to the NTT
 // domain (32.8 MB), the key-switching key as byte limbs for the int8 matrix
 // cores (50.3 MB), and the twiddle tables.  Gate batches run as two
 // launches on the caller's stream: blind rotation (with the gate prologue and
@@ -246,8 +246,6 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
     if ((e = hipMalloc((void**)&ctx->twf, 1024 * 8)) != hipSuccess) return fail(e, "twiddles");
     if ((e = hipMalloc((void**)&ctx->twi, 1024 * 8)) != hipSuccess) return fail(e, "twiddles");
     if ((e = hipMalloc((void**)&ctx->bkd, bkd_words * 8)) != hipSuccess) return fail(e, "bootstrapping key");
-    if ((e = hipMalloc((void**)&ctx->bkw, n * dev::kKeyStep * sizeof(dev::fft::cd))) != hipSuccess)
-        return fail(e, "bootstrapping key");
     if ((e = hipMalloc((void**)&ctx->bkc, n * dev::kKeyStep * sizeof(dev::fft::cd))) != hipSuccess)
         return fail(e, "bootstrapping key");
     if ((e = hipMalloc((void**)&ctx->bkn, n * dev::kKeyStep * sizeof(dev::fft::cd))) != hipSuccess)
@@ -269,7 +267,7 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
         return fail(e, "upload");
     if ((e = dev::launch_bk_prepare(bk_tmp, ctx->bkd, ctx->twf, (uint32_t)n, ctx->stream)) != hipSuccess)
         return fail(e, "bootstrapping key transform");
-    if ((e = dev::launch_bk_prepare_fft(bk_tmp, ctx->bkw, ctx->bkc, ctx->bkn, ctx->roots, (uint32_t)n, ctx->stream)) !=
+    if ((e = dev::launch_bk_prepare_fft(bk_tmp, ctx->bkc, ctx->bkn, ctx->roots, (uint32_t)n, ctx->stream)) !=
         hipSuccess)
         return fail(e, "bootstrapping key transform");
     if ((e = dev::launch_ksk_prepare(ksk_tmp, ctx->ksb, ctx->stream)) != hipSuccess)
@@ -284,7 +282,6 @@ extern "C" int fhe_ctx_create(const fhe_cloud_key* ck, int device, fhe_ctx** out
     ctx->keys.ksb = ctx->ksb;
     ctx->keys.twf = ctx->twf;
     ctx->keys.twi = ctx->twi;
-    ctx->keys.bkw = ctx->bkw;
     ctx->keys.bkc = ctx->bkc;
     ctx->keys.bkn = ctx->bkn;
     ctx->keys.roots = ctx->roots;
@@ -302,7 +299,7 @@ extern "C" void fhe_ctx_destroy(fhe_ctx* ctx) {
             for (hipEvent_t ev : tl.ev) ctx->event_pool.push_back(ev);
         for (hipEvent_t ev : ctx->event_pool) (void)hipEventDestroy(ev);
         for (void* p : {(void*)ctx->bkd, (void*)ctx->ksb, (void*)ctx->twf,
-                        (void*)ctx->twi, (void*)ctx->big, (void*)ctx->bkw, (void*)ctx->bkc, (void*)ctx->bkn, (void*)ctx->roots})
+                        (void*)ctx->twi, (void*)ctx->big, (void*)ctx->bkc, (void*)ctx->bkn, (void*)ctx->roots})
             if (p) (void)hipFree(p);
         if (ctx->stream) (void)hipStreamDestroy(ctx->stream);
         if (ctx->order) (void)hipEventDestroy(ctx->order);
@@ -464,7 +461,7 @@ extern "C" int fhe_debug_cmux(int device, int arith, const uint32_t* bk_i, int32
     }
     if (e == hipSuccess)
         step(arith == 0 ? dev::launch_bk_prepare(d_bk, d_bkd, d_twf, 1, nullptr)
-                        : dev::launch_bk_prepare_fft(d_bk, nullptr, nullptr, d_bkn, d_roots, 1, nullptr));
+                        : dev::launch_bk_prepare_fft(d_bk, nullptr, d_bkn, d_roots, 1, nullptr));
     dev::DeviceKeys K{};
     K.twf = d_twf;
     K.twi = d_twi;

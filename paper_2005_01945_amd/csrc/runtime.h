@@ -24,8 +24,7 @@ struct fhe_ctx {
     uint8_t* ksb = nullptr;
     uint64_t* twf = nullptr;
     uint64_t* twi = nullptr;
-    fhe::dev::fft::cd* bkw = nullptr;    // BK for the FFT products, three layouts
-    fhe::dev::fft::cd* bkc = nullptr;
+    fhe::dev::fft::cd* bkc = nullptr;    // BK for the FFT products, both layouts
     fhe::dev::fft::cd* bkn = nullptr;
     fhe::dev::fft::cd* roots = nullptr;  // exp(i pi k / 1024), k < 2048
     uint32_t* big = nullptr;  // extracted samples of the gates in flight, [gates][kSampleWords]

@@ -3,7 +3,7 @@
 // A circuit level is one batch of independent gates; its width decides how
 // the gates should be laid onto the chip.  Wide batches want one wavefront
 // per gate and two waves per SIMD (issued work per gate is what counts);
-// batches narrower than the chip want each gate's CMux chain split over two
+// batches narrower than the chip want each gate's CMux chain split over several
 // wavefronts (latency per gate is what counts).  The tuner measures every
 // shape at widths 1, 2, 4, ... and keeps the fastest per width bucket.
 #include <hip/hip_runtime.h>
@@ -44,11 +44,11 @@ int tune_bucket(size_t width) {
     return b;
 }
 
-// Before any measurement: FFT arithmetic everywhere; eight waves per gate (the
-// shape named four) up to one gate per CU, two waves per gate up to two, groups
-// of four gates beyond.  Measured blind rotations (ms) at 256 / 512 / 1,024
-// gates on 256 CUs: eight waves 1.9 / 3.4 / 6.9, two waves 2.7 / 3.2 / 6.3,
-// groups 4.5 / 4.5 / 4.5.
+// Before any measurement: FFT arithmetic everywhere; the one-gate-per-CU layout
+// up to one gate per CU, the two-gate one up to two, groups of four gates
+// beyond.  Measured blind rotations (ms) at 256 / 512 / 1,024 gates on 256 CUs:
+// one gate per CU 1.71 / 3.04 / 5.72, two 1.81 / 2.86 / 5.41, groups 4.5 / 4.5 /
+// 4.5.
 static dev::LaunchConfig default_shape(const fhe_ctx* ctx, size_t width) {
     const size_t cus = (size_t)ctx->cu_count;
     if (width <= cus) return dev::LaunchConfig{4, 1, 1};
