@@ -94,7 +94,7 @@ hipError_t launch_ksk_prepare(const uint32_t* ksk, uint8_t* ksb, hipStream_t s);
 // Gate prologue + blind rotation + sample extraction: writes big[g]
 // [kSampleWords] (big[2g], big[2g+1] with pair_slots).
 hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* big,
-                               uint32_t count, LaunchConfig cfg, hipStream_t s);
+                               uint32_t count, LaunchConfig cfg, uint32_t cus, hipStream_t s);
 
 // Key switching big[k] -> the gate's output sample, k < count (with
 // pair_slots, count = 2 * gates).

@@ -1129,13 +1129,13 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // modulo two primes that these replace: 3.2 ms (one gate) and 4.6 (512).
 template <bool LEAN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(LEAN ? 4 : 2, LEAN ? 4 : 2)))
-void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
+void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t first, uint32_t count) {
     __shared__ NarrowLds<LEAN> S;
     static_assert(!LEAN || 2 * sizeof(NarrowLds<LEAN>) <= 160 * 1024, "two gates per compute unit");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = wave >> 1, half = wave & 1;
     const int lane = threadIdx.x & 63, h = lane >> 5, t = lane & 31;
-    const uint32_t g = blockIdx.x;
+    const uint32_t g = first + blockIdx.x;
     if (g >= count) return;  // uniform over the block
     NarrowTwiddles T;
     load_narrow_twiddles(S, T, K.roots, wave, half, lane);
@@ -1708,18 +1708,54 @@ hipError_t launch_bk_prepare(const uint32_t* bk, uint64_t* bkd, const uint64_t* 
 // Arithmetic 1 with one wave per gate always runs groups of four gates: the
 // share of the key loads that a smaller group would lose costs more than its
 // idle waves (one gate: 4.8 ms in a group, 18.7 ms on a wave by itself).
+// How many gates at the end of a wide batch of `count` run on the narrow kernel
+// after the groups.  Groups fill the chip in rounds of eight gates per compute
+// unit; a last round of up to four per unit still takes 4.4 ms and one of more
+// 7.0 ms, and leaves most of the chip idle when it is short.  The narrow kernel
+// does one gate per unit in 1.7 ms and two in 2.9 (256 units; blind rotation, ms,
+// all groups / with a tail):
+//   rest up to 2 per unit:     2,049 gates 11.3 / 8.9, 2,560 gates 11.0 / 9.8,
+//                              16,385 gates 56.2 / 54.1
+//   rest over 4, to 5 per unit: 1,025 to 1,280 gates 7.1 / 6.0
+// Between 2 and 4 per unit the narrow kernel needs 4.4 ms or more itself, and
+// past 5 per unit the two parts (4.5 + 2.9) are slower than one round.
+static uint32_t narrow_tail(uint32_t count, uint32_t cus) {
+    const uint32_t rest = count % (8 * cus);
+    if (count > rest && rest <= 2 * cus) return rest;
+    if (rest > 4 * cus && rest <= 5 * cus) return rest - 4 * cus;
+    return 0;
+}
+
 hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* big,
-                               uint32_t count, LaunchConfig cfg, hipStream_t s) {
+                               uint32_t count, LaunchConfig cfg, uint32_t cus, hipStream_t s) {
     if (count == 0) return hipSuccess;
     auto launch = [&](auto kernel, uint32_t gates, uint32_t threads) {
         hipLaunchKernelGGL(kernel, dim3((count + gates - 1) / gates), dim3(threads), 0, s, K, io, big, count);
         return hipGetLastError();
     };
+    // gates first .. count - 1, one per block
+    auto launch_narrow = [&](uint32_t first, bool lean) {
+        const dim3 grid(count - first), block(512);
+        if (lean)
+            hipLaunchKernelGGL(k_blind_rotate_narrow<true>, grid, block, 0, s, K, io, big, first, count);
+        else
+            hipLaunchKernelGGL(k_blind_rotate_narrow<false>, grid, block, 0, s, K, io, big, first, count);
+        return hipGetLastError();
+    };
     if (cfg.arith == 1) {
         switch (cfg.waves_per_gate) {
-        case 1: return launch(k_blind_rotate_group, 4, 256);
-        case 2: return launch(k_blind_rotate_narrow<true>, 1, 512);
-        case 4: return launch(k_blind_rotate_narrow<false>, 1, 512);
+        case 1: {
+            const uint32_t tail = narrow_tail(count, cus);
+            if (tail) {
+                hipLaunchKernelGGL(k_blind_rotate_group, dim3((count - tail) / 4), dim3(256), 0, s, K, io, big,
+                                   count - tail);
+                const hipError_t e = hipGetLastError();
+                return e == hipSuccess ? launch_narrow(count - tail, tail > cus) : e;
+            }
+            return launch(k_blind_rotate_group, 4, 256);
+        }
+        case 2: return launch_narrow(0, true);
+        case 4: return launch_narrow(0, false);
         default: return hipErrorInvalidValue;
         }
     }

@@ -75,7 +75,7 @@ extern "C" int fhe_bootstrap_gate_batch_noalloc(fhe_ctx* ctx, const uint8_t* ops
     io.out = out;
     io.err = ctx->err_dev;
     const dev::LaunchConfig cfg = launch_config_for(ctx, count);
-    e = dev::launch_blind_rotate(ctx->keys, io, ctx->noalloc_scratch, (uint32_t)count, cfg, s);
+    e = dev::launch_blind_rotate(ctx->keys, io, ctx->noalloc_scratch, (uint32_t)count, cfg, (uint32_t)ctx->cu_count, s);
     if (e == hipSuccess) e = dev::launch_key_switch(ctx->keys, io, ctx->noalloc_scratch, (uint32_t)count, s);
     rc = e == hipSuccess ? FHE_OK : hip_fail(e, "fhe_bootstrap_gate_batch_noalloc");
     return capturing ? rc : order_end(ctx, s, rc);

@@ -168,7 +168,7 @@ int run_gate_batch(fhe_ctx* ctx, const dev::GateIO& io_in, size_t count, hipStre
             if (!(ev = take_event(ctx))) return set_error(FHE_EDEVICE, "timing event creation failed");
         (void)hipEventRecord(tl.ev[0], s);
     }
-    hipError_t e = dev::launch_blind_rotate(ctx->keys, io, ctx->big, (uint32_t)count, cfg, s);
+    hipError_t e = dev::launch_blind_rotate(ctx->keys, io, ctx->big, (uint32_t)count, cfg, (uint32_t)ctx->cu_count, s);
     if (e != hipSuccess) return hip_fail(e, "blind rotation launch");
     if (ctx->timing) (void)hipEventRecord(tl.ev[1], s);
     e = dev::launch_key_switch(ctx->keys, io, ctx->big, (uint32_t)samples, s);

@@ -135,7 +135,7 @@ extern "C" int fhe_ctx_autotune(fhe_ctx* ctx, uint32_t max_width, uint32_t reps)
             float fastest = 0;
             for (uint32_t r = 0; r <= reps && e == hipSuccess; ++r) {  // run 0 warms up
                 e = hipEventRecord(ev[0], ctx->stream);
-                if (e == hipSuccess) e = dev::launch_blind_rotate(ctx->keys, io, ctx->big, width, cfg, ctx->stream);
+                if (e == hipSuccess) e = dev::launch_blind_rotate(ctx->keys, io, ctx->big, width, cfg, (uint32_t)ctx->cu_count, ctx->stream);
                 if (e == hipSuccess) e = dev::launch_key_switch(ctx->keys, io, ctx->big, width, ctx->stream);
                 if (e == hipSuccess) e = hipEventRecord(ev[1], ctx->stream);
                 if (e == hipSuccess) e = hipEventSynchronize(ev[1]);
