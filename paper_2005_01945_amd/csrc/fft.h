@@ -121,11 +121,11 @@ __device__ __forceinline__ void butterfly_c(cd& a, cd& b) {
 }
 
 // Forward on R registers below the root n = 256 (X^512 = i), whose twiddles
-// are the same for every lane.
-template <int R>
+// are the same for every lane, from level FROM on.
+template <int R, int FROM = 0>
 __device__ __forceinline__ void forward_root(cd (&x)[R]) {
     constexpr int L = __builtin_ctz(R);
-    unroll<0, L>([&](auto l_) {
+    unroll<FROM, L>([&](auto l_) {
         constexpr int l = decltype(l_)::value, m = R >> (l + 1);
         unroll<0, (1 << l)>([&](auto c_) {
             constexpr int c = decltype(c_)::value;

@@ -162,16 +162,6 @@ __device__ __forceinline__ const lds_u32* lds_column(const uint32_t* a, int t) {
     return p;
 }
 
-// Word of X^ai ACC's coefficient m before its sign, from d4 = 4 (m - ai) and
-// the polynomial's LDS byte address (a multiple of 4096).  d4 needs no
-// reduction: its bits 2..11 are (m - ai) mod 1024 times 4, the byte offset of
-// the word read (the address is one AND-OR), and its bit 12 tells whether
-// (m - ai) mod 2048 >= 1024 (X^N = -1: the word is negated), for negative
-// m - ai too.
-__device__ __forceinline__ uint32_t rotated_word(uint32_t abase, int d4) {
-    return *(const lds_u32*)(uintptr_t)(((uint32_t)d4 & 0xFFCu) | abase);
-}
-
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -407,15 +397,6 @@ __device__ __forceinline__ void fft512_forward(cd (&x)[8], cd* ex, const LaneTwi
     fft::forward_lane<8>(x, [&](auto k) { return W.f2[decltype(k)::value]; });
     wave_exchange<9, 1>(x, ex + hi * 72 + lo, ex + hi * 72 + 9 * lo);
     fft::forward_lane<8>(x, [&](auto k) { return W.f3[decltype(k)::value]; });
-}
-
-// D = X^ai ACC - ACC plus the rounding offset of both digits, of coefficient
-// m with d4 = 4 (m - ai) (see rotated_word), with the top bit of each digit's
-// field flipped so that the signed 10-bit fields at 22 and 12 are the digits.
-__device__ __forceinline__ uint32_t digit_word(uint32_t v, uint32_t own, int d4) {
-    uint32_t sgn;  // (the optimiser would turn the bit-field extract into a compare and a select)
-    asm("v_bfe_i32 %0, %1, 12, 1" : "=v"(sgn) : "v"(d4));
-    return (((v + sgn) ^ sgn) + (kDecompOffset - own)) ^ 0x80200000u;
 }
 
 __device__ __forceinline__ void mac(cd& o, const cd& k, const cd& x) {
@@ -1187,21 +1168,29 @@ void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, 
 // Between the steps the accumulators are in registers and pass through the
 // same LDS to be read rotated.
 //
-// Bound by issue: about 2,310 VALU (1,860 of them f64 at 4.6-5.1 cycles) and
-// 128 matrix instructions of 16 cycles per wave and step, 12,800 of the 16,400
+// Bound by issue: about 2,220 VALU (1,830 of them f64 at 4.6-5.1 cycles) and
+// 128 matrix instructions of 16 cycles per wave and step, 12,500 of the 15,000
 // cycles that a step takes per wave at two waves per SIMD; LDS is busy a third
-// of the time, its writes (64 B per clock) most of it.  16,384 gates in 53 ms,
-// 2,048 in 7.2 ms, 1,024 (one wave per SIMD) in 4.5 ms; the integer
-// NTTs modulo two 28-bit primes that this replaces issued 6,570 VALU per wave
-// and step: 100, 12.5 and 8.1 ms.
+// of the time, its writes (64 B per clock) most of it.  16,384 gates in 51 ms,
+// 2,048 in 7.2 ms, 1,024 (one wave per SIMD) in 4.5 ms.  With a masked address
+// and a sign of its own for each rotated word, and the first level in doubles:
+// 2,310 VALU, 52.0 ms (with the reads spread among the arithmetic 53.7).  The
+// integer NTTs modulo two 28-bit primes that this replaces issued 6,570 VALU per
+// wave and step: 100, 12.5 and 8.1 ms.
 constexpr int kRowBytes = 32 * 8 + 16;  // 16-byte skew: lanes of layout B read 16 rows at once
 
-struct alignas(4096) GroupLds {
-    char buf[256 * kRowBytes];  // also the accumulators (8 KB per wave) during the extraction
+struct alignas(16) GroupLds {
+    char buf[256 * kRowBytes];  // also the accumulators, each wave's in its own rows, during the extraction
     cd tabf[16][16];            // twiddle k of block Q (forward levels 5..9)
     cd tabi[32][16];            // inverse factor of coefficient t, block Q
 };
 static_assert(2 * sizeof(GroupLds) <= 160 * 1024, "two groups per compute unit");
+
+// An accumulator polynomial to be read rotated by any amount at fixed offsets
+// from one address: ACC, then -ACC.  (The skew sends the lanes' two polynomials
+// to different banks.)
+constexpr int kAccWords = 2 * N + 32;
+static_assert(2 * kAccWords * 4 <= 64 * kRowBytes, "accumulators fit the wave's own rows");
 
 constexpr int kStaged = 12;  // key loads of a step that go through LDS
 constexpr int KW = 8;        // window of the others, in registers
@@ -1236,7 +1225,8 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
         S.tabi[m][Q] = conj_root(K.roots, m * (1 + 4 * fft::brv(Q, 4)));
     }
     char* buf = S.buf;
-    uint32_t (&accl)[2][1024] = *reinterpret_cast<uint32_t (*)[2][1024]>(buf + 8192 * w);
+    char* own = buf + 64 * kRowBytes * w;  // this wave's own rows
+    uint32_t (&accl)[2][kAccWords] = *reinterpret_cast<uint32_t (*)[2][kAccWords]>(own);
     const uint32_t g = blockIdx.x * 4 + w;
     const bool live = g < count;  // a missing gate's wave still serves the others' spectrum
     uint32_t ab[8] = {}, acc[32] = {};
@@ -1257,9 +1247,9 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
     const cd* keyw = K.bkc + 64 * w;  // this wave's keys of the step
     const cd* key = keyw + lane;
     const uint32_t lane16 = 16 * lane;
-    const uint32_t kslot = (uint32_t)(uintptr_t)(const lds_u32*)(const uint32_t*)(buf + 64 * w * kRowBytes);
-    const char* kread = buf + 64 * w * kRowBytes + 16 * lane;
-    const uint32_t abase = (uint32_t)(uintptr_t)(const lds_u32*)accl[h];
+    const uint32_t kslot = (uint32_t)(uintptr_t)(const lds_u32*)(const uint32_t*)own;
+    const char* kread = own + 16 * lane;
+    uint32_t* accw = &accl[h][t];
     auto col_at = [&](auto d, auto q) -> double& {
         constexpr int Q = decltype(q)::value;
         return *reinterpret_cast<double*>(colA + (64 * (Q >> 2) + 16 * decltype(d)::value + 4 * (Q & 3)) * kRowBytes);
@@ -1268,33 +1258,45 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
     for (int i = 0; i < NLWE; ++i) {
         const int ai = __builtin_amdgcn_readlane(ab[0], i & 63);
         cd x[2][16], y[32];
-        // digits of D = X^ai ACC - ACC, both of each coefficient
+        // digits of D = X^ai ACC - ACC, both of each coefficient.  X^ai ACC is
+        // the words of (ACC, -ACC) from (-ai) mod N on, or their negatives, for
+        // every lane alike; the fences keep all reads ahead of the arithmetic.
 #pragma unroll
-        for (int e = 0; e < 32; ++e) accl[h][t + 32 * e] = acc[e];
+        for (int e = 0; e < 32; ++e) {
+            accw[32 * e] = acc[e];
+            accw[32 * e + N] = 0u - acc[e];
+        }
         wave_lds_sync();
         {
-            const int d4 = 4 * (t - ai);
+            const uint32_t sgn = (uint32_t)((int32_t)((uint32_t)(-ai) << 21) >> 31), off = kDecompOffset - sgn;
+            const uint32_t* rot = accw + (-ai & (N - 1));
+            uint32_t v[32];
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                uint32_t v[16];
+            for (int e = 0; e < 32; ++e) v[e] = rot[32 * e];
+            sched_fence();
 #pragma unroll
-                for (int k = 0; k < 16; ++k) v[k] = rotated_word(abase, d4 + 128 * (16 * c + k));
+            for (int k = 0; k < 8; ++k) {
+                uint32_t z[4];  // top bit of each digit's field flipped: the signed 10-bit fields are the digits
 #pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const uint32_t z = digit_word(v[k], acc[16 * c + k], d4 + 128 * (16 * c + k));
+                for (int q = 0; q < 4; ++q)
+                    z[q] = ((v[k + 8 * q] ^ sgn) + (off - acc[k + 8 * q])) ^ 0x80200000u;
 #pragma unroll
-                    for (int d = 0; d < 2; ++d) {
-                        const double dg = (double)(int32_t)__builtin_amdgcn_sbfe((int32_t)z, 22 - 10 * d, 10);
-                        if (c == 0)
-                            x[d][k].x = dg;
-                        else
-                            x[d][k].y = dg;
-                    }
+                for (int d = 0; d < 2; ++d) {
+                    int32_t g[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) g[q] = (int32_t)__builtin_amdgcn_sbfe((int32_t)z[q], 22 - 10 * d, 10);
+                    // first level: (a, b) -> a +- b (1 + i) / sqrt 2, the sums in integers
+                    constexpr double c = fft::kCos[8];
+                    const double re = (double)g[0], im = (double)g[2];
+                    const double br = (double)(g[1] - g[3]), bi = (double)(g[1] + g[3]);
+                    x[d][k] = {__builtin_fma(c, br, re), __builtin_fma(c, bi, im)};
+                    x[d][k + 8] = {__builtin_fma(-c, br, re), __builtin_fma(-c, bi, im)};
                 }
             }
+            sched_fence();
         }
-        fft::forward_root<16>(x[0]);
-        fft::forward_root<16>(x[1]);
+        fft::forward_root<16, 1>(x[0]);
+        fft::forward_root<16, 1>(x[1]);
         lds_barrier();  // every wave has read its accumulator
         static_for<0, 2>([&](auto d) { static_for<0, 16>([&](auto q) { col_at(d, q) = x[d][q].x; }); });
         lds_barrier();
