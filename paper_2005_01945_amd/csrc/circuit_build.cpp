@@ -373,16 +373,18 @@ std::vector<uint32_t> asap_levels(const Circuit& c, uint32_t* depth) {
 }
 
 // Relative time of one launch of `gates` gates, in units of one round of the
-// widest launch shape (`round` gates: eight per compute unit, two waves per
-// SIMD), from the measured shape timings: a level of at most an eighth, a
-// quarter or half a round runs on the narrower shapes in about 0.27, 0.36 and
-// 0.64 of a round's time; wider levels take whole rounds.
+// widest launch shape (`round` gates: eight per compute unit, 7.0 ms on 256),
+// from the measured shape timings: what is left over after the whole rounds
+// runs on the narrower shapes or as a part of a round.  Up to an eighth of a
+// round takes 1.72 ms, a quarter 2.87, a half 4.45, five eighths 6.0.
 static double level_cost(uint64_t gates, uint64_t round) {
-    if (gates == 0) return 0.0;
-    if (8 * gates <= round) return 0.27;
-    if (4 * gates <= round) return 0.36;
-    if (2 * gates <= round) return 0.64;
-    return (double)((gates + round - 1) / round);
+    const uint64_t rest = gates % round;
+    const double whole = (double)(gates / round);
+    if (rest == 0) return whole;
+    if (8 * rest <= round) return whole + 0.25;
+    if (4 * rest <= round) return whole + 0.41;
+    if (2 * rest <= round) return whole + 0.64;
+    return whole + (8 * rest <= 5 * round ? 0.87 : 1.0);
 }
 
 // List scheduling against the launch rounds: level by level, the ready gates
