@@ -13,12 +13,13 @@
 // rounding the computed real number to the nearest integer recovers it: with
 // u = 2^-53, a butterfly of two fused multiply-adds per component (see
 // butterfly()) adds an error of at most 5.8 u of its outputs' Euclidean norm
-// (twiddles are correctly rounded), so nine levels add 52 u, in the digits'
-// transform, in the key's and in the inverse alike; the multiply-add over
-// four rows and the final twist add less than 16 u.  The Euclidean norms are
-// at most 2^9 * 2^5 (digits) and 2^15 * 2^5 (key half) per row, and a
-// coefficient of a product is at most the product of the norms: the error is
-// below 4 * 2^14 * 2^20 * 172 u = 172 * 2^-17 < 0.0014, where 0.5 would be
+// (twiddles are correctly rounded; the digits' first level, on sums of
+// integers, less), so nine levels add 52 u, in the digits' transform, in the
+// key's and in the inverse alike; the multiply-add over four rows and the final
+// twist add less than 16 u.  The Euclidean norms are at most 2^9 * 2^5 (digits)
+// and 2^15 * 2^5 (key half) per row, and a coefficient of a product is at most
+// the product of the norms: the error is below
+// 4 * 2^14 * 2^20 * 172 u = 172 * 2^-17 < 0.0014, where 0.5 would be
 // needed to round wrongly.  The result V_lo + 2^16 V_hi mod 2^32 is therefore
 // the definition's, bit for bit.
 //
