@@ -1100,7 +1100,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // that leave compute units with one gate (LEAN = false: one gate 1.40 ms, 256
 // gates 1.71 ms) or two (LEAN: 512 gates 2.86 ms, 300 gates 2.60).  A step of
 // one gate takes 6,700 cycles, a chain of LDS round trips and four barriers
-// around 430 VALU per wave; two waves per SIMD fill each other's gaps.  With
+// around 495 VALU per wave; two waves per SIMD fill each other's gaps.  With
 // two gates LDS is busy 70% of the time, most of it writes (64 B per clock).
 // Both exchanges of lane bits 3 to 0 through LDS: 1.53 and 3.08 ms (bits 1 and
 // 0 by moves as well, which need selects: 1.46 and 2.96).  The 128 KB of key
@@ -1199,8 +1199,9 @@ static_assert(3 * 64 * kRowBytes + kStaged * 1024 <= 65536, "and below 64 KB of 
 
 // Starts the copy of 1 KB of key (the lanes' 16 bytes at byte offset `off`)
 // from memory to LDS byte address `dst`, which must be below 64 KB (M0 holds
-// its low 16 bits; the compiler keeps nothing in M0).  The compiler does not count the copy: the reader waits
-// for every load (vmcnt(0)) before it reads the bytes.
+// its low 16 bits; the compiler keeps nothing in M0).  The compiler does not
+// count the copy: the reader waits for every load (vmcnt(0)) before it reads the
+// bytes.
 __device__ __forceinline__ void load_key_lds(const cd* __restrict__ src, uint32_t off, uint32_t dst) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  ::"s"(dst), "v"(off), "s"(src) : "memory");
