@@ -31,6 +31,7 @@
 // and half h accumulates output column h against BK_i in the NTT domain.
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <type_traits>
 
 #include "fhe_internal.h"
@@ -1195,17 +1196,23 @@ static_assert(2 * kAccWords * 4 <= 64 * kRowBytes, "accumulators fit the wave's 
 constexpr int kStaged = 12;  // key loads of a step that go through LDS
 constexpr int KW = 8;        // window of the others, in registers
 static_assert(kStaged % 4 == 0 && kStaged * 1024 <= 64 * kRowBytes, "staged keys fit the wave's own rows");
-static_assert(3 * 64 * kRowBytes + kStaged * 1024 <= 65536, "and below 64 KB of LDS");
+// (The group kernel's only shared object starts at LDS address 0.)
+static_assert(offsetof(GroupLds, buf) + 3 * 64 * kRowBytes + kStaged * 1024 <= 65536, "and below 64 KB of LDS");
 
 // Starts the copy of 1 KB of key (the lanes' 16 bytes at byte offset `off`)
 // from memory to LDS byte address `dst`, which must be below 64 KB (M0 holds
-// its low 16 bits; the compiler keeps nothing in M0).  The compiler does not
+// its low 16 bits).  M0 is declared as written, so that no pass keeps a value of
+// its own in it across the copy; it is a reserved register, which the compiler
+// warns of because it would not save one either.  The compiler does not
 // count the copy: the reader waits for every load (vmcnt(0)) before it reads the
 // bytes.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_key_lds(const cd* __restrict__ src, uint32_t off, uint32_t dst) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 ::"s"(dst), "v"(off), "s"(src) : "memory");
+                 ::"s"(dst), "v"(off), "s"(src) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
