@@ -324,8 +324,8 @@ def roofline_of(records):
     avg_launch_ms = dom["ms"] / dom["launches"]
     achieved = LANE_OPS_PER_GATE[shape[2]] * gates_per_launch / (avg_launch_ms / 1e3) / 1e12
     if shape[2] == 1:
-        kernel = {1: "k_blind_rotate_group", 2: "k_blind_rotate_narrow<true>",
-                  4: "k_blind_rotate_narrow<false>"}[shape[0]]
+        kernel = {1: "k_blind_rotate_group<false>", 2: "k_blind_rotate_narrow<true, false>",
+                  4: "k_blind_rotate_narrow<false, false>"}[shape[0]]
     else:
         kernel = "k_blind_rotate_pair" if shape[0] == 2 else f"k_blind_rotate<{shape[1]}>"
     roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": round(VALU_PEAK_TOPS, 2),

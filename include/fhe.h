@@ -517,12 +517,19 @@ int fhe_ctx_timing_launches(fhe_ctx* ctx, fhe_launch_record* out, size_t max, si
 /* Message of the last failing call on this thread ("" if none). */
 const char* fhe_last_error(void);
 
-/* Test entry: one CMux step of the blind rotation on explicit HOST data,
- * computed on `device` with the production kernels of arithmetic `arith`
- * (0: Goldilocks NTT, 1: FFT; see fhe_launch_config):
+/* Test entries: one CMux step of the blind rotation on explicit HOST data,
+ * computed on `device`:
  *   acc[2][N] <- acc + BK_i [x] (X^abar acc - acc),
- * bk_i: uint32 [2l][2][N] (coefficient domain, rows r = 2j + p). */
+ * bk_i: uint32 [2l][2][N] (coefficient domain, rows r = 2j + p).
+ * fhe_debug_cmux_shape runs the step of the kernel that launch shape `cfg` (see
+ * fhe_launch_config) uses: arith 1 the groups of four gates (all four step the
+ * same acc; FHE_EDEVICE if they disagree), the two-gates-per-unit or the
+ * one-gate-per-unit kernel; arith 0 the one-wave step, whose two passes the
+ * two-wave shape runs side by side.  fhe_debug_cmux is the shape {1, 1, 0} for
+ * arith 0 and {4, 1, 1} for arith 1. */
 int fhe_debug_cmux(int device, int arith, const uint32_t* bk_i, int32_t abar, uint32_t* acc);
+int fhe_debug_cmux_shape(int device, const fhe_launch_config* cfg, const uint32_t* bk_i, int32_t abar,
+                         uint32_t* acc);
 
 /* Measurement entry: the issue rate of one VALU instruction class on
  * `device`, in 32-bit lane operations per second (every lane of eight waves

@@ -108,6 +108,7 @@ _SIGS = {
     "fhe_serve_destroy": (None, [_vp]),
     "fhe_last_error": (C.c_char_p, []),
     "fhe_debug_cmux": (C.c_int, [C.c_int, C.c_int, _vp, C.c_int32, _vp]),
+    "fhe_debug_cmux_shape": (C.c_int, [C.c_int, C.POINTER(fhe_launch_config), _vp, C.c_int32, _vp]),
     "fhe_debug_valu_rate": (C.c_int, [C.c_int, C.c_int, C.POINTER(C.c_double)]),
     "fhe_debug_plan": (C.c_int, [_vp, C.c_int, C.c_uint32, C.c_uint32, C.c_uint32, C.c_uint64, _vp, C.c_uint64,
                                  _vp, C.c_uint32, C.POINTER(C.c_uint64), C.POINTER(C.c_uint32)]),
@@ -537,11 +538,20 @@ def fhe_serve_stats(srv):
 
 
 def fhe_debug_cmux(bk_i, abar, acc, device=0, arith=0):
-    """One CMux step on host arrays with the production kernels of
-    arithmetic `arith` (test entry)."""
+    """One CMux step on host arrays in arithmetic `arith`, 1 with the kernel for
+    one gate per compute unit (test entry)."""
     b, pb = _host(bk_i, np.uint32)
     a = np.ascontiguousarray(acc, np.uint32).copy()
     _check(lib().fhe_debug_cmux(device, arith, pb, abar, a.ctypes.data), "fhe_debug_cmux")
+    return a
+
+
+def fhe_debug_cmux_shape(bk_i, abar, acc, shape, device=0):
+    """The same with the step of the kernel that launch shape `shape` uses."""
+    b, pb = _host(bk_i, np.uint32)
+    a = np.ascontiguousarray(acc, np.uint32).copy()
+    c = fhe_launch_config(*shape)
+    _check(lib().fhe_debug_cmux_shape(device, C.byref(c), pb, abar, a.ctypes.data), "fhe_debug_cmux_shape")
     return a
 
 

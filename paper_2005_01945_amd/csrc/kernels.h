@@ -101,10 +101,11 @@ hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* 
 hipError_t launch_key_switch(const DeviceKeys& K, const GateIO& io, const uint32_t* big,
                              uint32_t count, hipStream_t s);
 
-// One CMux on acc[2][N] (device) with prepared BK_i (one iteration of bkd
-// for arith 0, K.bkn for arith 1).
-hipError_t launch_debug_cmux(const DeviceKeys& K, int arith, const uint64_t* bk_i, int32_t abar,
-                             uint32_t* acc, hipStream_t s);
+// One CMux with the step of the kernel that shape cfg launches, in place on
+// accumulators in device memory: acc[4][2][N] for the groups of four gates
+// (arith 1, waves_per_gate 1), acc[2][N] for the others.  K holds one CMux of key:
+// bkd, bkc or bkn.
+hipError_t launch_debug_cmux(const DeviceKeys& K, LaunchConfig cfg, int32_t abar, uint32_t* acc, hipStream_t s);
 
 // Issue-rate probe of VALU instruction class `op` (0 v_add_u32, 1
 // v_mul_lo_u32, 2 v_mad_i64_i32, 3 v_mul_hi_u32, 4 v_bfe_i32, 5

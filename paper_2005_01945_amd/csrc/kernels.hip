@@ -1109,7 +1109,9 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // are spread over the step: all in one place they cost 0.3 ms.  Four wavefronts
 // per gate, one per row: 2.06 and 4.2 ms; two: 2.54 and 3.3.  The integer NTTs
 // modulo two primes that these replace: 3.2 ms (one gate) and 4.6 (512).
-template <bool LEAN>
+// STEP: one CMux with K.bkn instead of the whole bootstrap, on the accumulator at
+// big ([2][N], in place), rotated by `first`.
+template <bool LEAN, bool STEP>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(LEAN ? 4 : 2, LEAN ? 4 : 2)))
 void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t first, uint32_t count) {
     __shared__ NarrowLds<LEAN> S;
@@ -1118,14 +1120,17 @@ void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, 
     const int row = wave >> 1, half = wave & 1;
     const int lane = threadIdx.x & 63, h = lane >> 5, t = lane & 31;
     const uint32_t g = first + blockIdx.x;
-    if (g >= count) return;  // uniform over the block
+    if (!STEP && g >= count) return;  // uniform over the block
     NarrowTwiddles T;
     load_narrow_twiddles(S, T, K.roots, wave, half, lane);
     uint32_t ab[8];
-    const int bbar = gate_prologue(io, g, lane, ab);
+    const int bbar = STEP ? 0 : gate_prologue(io, g, lane, ab);
     uint32_t (&acc)[2][kPad + 1024] = S.view();
     if (wave == 0) {
-        acc_init(acc, bbar, h, t, io.tv, gate_mu(io, g));
+        if constexpr (STEP)
+            for (int k = lane; k < 2 * N; k += 64) acc[k / N][k % N] = big[k];
+        else
+            acc_init(acc, bbar, h, t, io.tv, gate_mu(io, g));
         wave_lds_sync();
 #pragma unroll
         for (int p = 0; p < 2; ++p) S.acc[p][lane] = 0u - acc[p][960 + lane];
@@ -1135,6 +1140,11 @@ void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, 
 #pragma unroll
     for (int k = 0; k < 2; ++k) load_narrow_keys(ka[k], key, (row + k) & 3, row, half, lane);
     __syncthreads();
+    if constexpr (STEP) {
+        narrow_step(S, (int)first, key, key, ka, T, row, half, lane);
+        for (int k = threadIdx.x; k < 2 * N; k += 512) big[k] = acc[k / N][k % N];
+        return;
+    }
 #pragma unroll 1
     for (int b = 0; b < NLWE; b += 64) {
 #pragma unroll 1
@@ -1214,6 +1224,9 @@ __device__ __forceinline__ void load_key_lds(const cd* __restrict__ src, uint32_
 }
 #pragma clang diagnostic pop
 
+// STEP: one CMux with K.bkc instead of the whole bootstrap, on four accumulators
+// at big ([4][2][N], in place), rotated by `count`.
+template <bool STEP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, uint32_t count) {
     __shared__ GroupLds S;
@@ -1236,9 +1249,12 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
     char* own = buf + 64 * kRowBytes * w;  // this wave's own rows
     uint32_t (&accl)[2][kAccWords] = *reinterpret_cast<uint32_t (*)[2][kAccWords]>(own);
     const uint32_t g = blockIdx.x * 4 + w;
-    const bool live = g < count;  // a missing gate's wave still serves the others' spectrum
+    const bool live = STEP || g < count;  // a missing gate's wave still serves the others' spectrum
     uint32_t ab[8] = {}, acc[32] = {};
-    if (live) {
+    if constexpr (STEP) {
+#pragma unroll
+        for (int e = 0; e < 32; ++e) acc[e] = big[(2 * w + h) * N + t + 32 * e];
+    } else if (live) {
         const int bbar = gate_prologue(io, g, lane, ab);
         acc_init(accl, bbar, h, t, io.tv, gate_mu(io, g));
         wave_lds_sync();
@@ -1263,8 +1279,8 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
         return *reinterpret_cast<double*>(colA + (64 * (Q >> 2) + 16 * decltype(d)::value + 4 * (Q & 3)) * kRowBytes);
     };
 #pragma unroll 1
-    for (int i = 0; i < NLWE; ++i) {
-        const int ai = __builtin_amdgcn_readlane(ab[0], i & 63);
+    for (int i = 0; i < (STEP ? 1 : NLWE); ++i) {
+        const int ai = STEP ? (int)count : __builtin_amdgcn_readlane(ab[0], i & 63);
         cd x[2][16], y[32];
         // digits of D = X^ai ACC - ACC, both of each coefficient.  X^ai ACC is
         // the words of (ACC, -ACC) from (-ai) mod N on, or their negatives, for
@@ -1402,6 +1418,11 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
             for (int r = 0; r < 7; ++r) ab[r] = ab[r + 1];
         }
     }
+    if constexpr (STEP) {
+#pragma unroll
+        for (int e = 0; e < 32; ++e) big[(2 * w + h) * N + t + 32 * e] = acc[e];
+        return;
+    }
     if (!live) return;
 #pragma unroll
     for (int e = 0; e < 32; ++e) accl[h][t + 32 * e] = acc[e];
@@ -1447,25 +1468,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_bk_prepare_fft(const uint32_t
             if (bkc) bkc[(size_t)i * kKeyStep + ((leaf % 32) * 4 + leaf / 128) * 64 + 16 * r + 4 * (leaf / 32 % 4) + o] = v;
         }
     }
-}
-
-// One CMux on acc[2][N] in global memory with the FFT products (eight waves).
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_debug_cmux_fft(DeviceKeys K, int32_t abar, uint32_t* __restrict__ accg) {
-    __shared__ NarrowLds<false> S;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int row = wave >> 1, half = wave & 1;
-    NarrowTwiddles T;
-    load_narrow_twiddles(S, T, K.roots, wave, half, lane);
-    cd ka[4][4];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) load_narrow_keys(ka[k], K.bkn, (row + k) & 3, row, half, lane);
-    uint32_t (&acc)[2][kPad + 1024] = S.view();
-    for (int k = threadIdx.x; k < 2 * N; k += 512) acc[k / N][k % N] = accg[k];
-    for (int k = threadIdx.x; k < 2 * kPad; k += 512) S.acc[k / kPad][k % kPad] = 0u - accg[k / kPad * N + 960 + k % kPad];
-    __syncthreads();
-    narrow_step(S, abar, K.bkn, K.bkn, ka, T, row, half, lane);
-    for (int k = threadIdx.x; k < 2 * N; k += 512) accg[k] = acc[k / N][k % N];
 }
 
 // Key switching N -> n: out = (0, b') - sum_{i,j} KSK[i][j][d_ij], d_ij the
@@ -1747,9 +1749,9 @@ hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* 
     auto launch_narrow = [&](uint32_t first, bool lean) {
         const dim3 grid(count - first), block(512);
         if (lean)
-            hipLaunchKernelGGL(k_blind_rotate_narrow<true>, grid, block, 0, s, K, io, big, first, count);
+            hipLaunchKernelGGL((k_blind_rotate_narrow<true, false>), grid, block, 0, s, K, io, big, first, count);
         else
-            hipLaunchKernelGGL(k_blind_rotate_narrow<false>, grid, block, 0, s, K, io, big, first, count);
+            hipLaunchKernelGGL((k_blind_rotate_narrow<false, false>), grid, block, 0, s, K, io, big, first, count);
         return hipGetLastError();
     };
     if (cfg.arith == 1) {
@@ -1757,12 +1759,12 @@ hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* 
         case 1: {
             const uint32_t tail = narrow_tail(count, cus);
             if (tail) {
-                hipLaunchKernelGGL(k_blind_rotate_group, dim3((count - tail) / 4), dim3(256), 0, s, K, io, big,
+                hipLaunchKernelGGL(k_blind_rotate_group<false>, dim3((count - tail) / 4), dim3(256), 0, s, K, io, big,
                                    count - tail);
                 const hipError_t e = hipGetLastError();
                 return e == hipSuccess ? launch_narrow(count - tail, tail > cus) : e;
             }
-            return launch(k_blind_rotate_group, 4, 256);
+            return launch(k_blind_rotate_group<false>, 4, 256);
         }
         case 2: return launch_narrow(0, true);
         case 4: return launch_narrow(0, false);
@@ -1816,12 +1818,17 @@ hipError_t launch_ksk_prepare(const uint32_t* ksk, uint8_t* ksb, hipStream_t s) 
     return hipGetLastError();
 }
 
-hipError_t launch_debug_cmux(const DeviceKeys& K, int arith, const uint64_t* bk_i, int32_t abar,
-                             uint32_t* acc, hipStream_t s) {
-    if (arith == 1)
-        hipLaunchKernelGGL(k_debug_cmux_fft, dim3(1), dim3(512), 0, s, K, abar, acc);
+hipError_t launch_debug_cmux(const DeviceKeys& K, LaunchConfig cfg, int32_t abar, uint32_t* acc, hipStream_t s) {
+    const GateIO io{};
+    const uint32_t ai = (uint32_t)abar;
+    if (cfg.arith == 0)
+        hipLaunchKernelGGL(k_debug_cmux, dim3(1), dim3(64), 0, s, K, K.bkd, abar, acc);
+    else if (cfg.waves_per_gate == 1)
+        hipLaunchKernelGGL(k_blind_rotate_group<true>, dim3(1), dim3(256), 0, s, K, io, acc, ai);
+    else if (cfg.waves_per_gate == 2)
+        hipLaunchKernelGGL((k_blind_rotate_narrow<true, true>), dim3(1), dim3(512), 0, s, K, io, acc, ai, 0u);
     else
-        hipLaunchKernelGGL(k_debug_cmux, dim3(1), dim3(64), 0, s, K, bk_i, abar, acc);
+        hipLaunchKernelGGL((k_blind_rotate_narrow<false, true>), dim3(1), dim3(512), 0, s, K, io, acc, ai, 0u);
     return hipGetLastError();
 }
 

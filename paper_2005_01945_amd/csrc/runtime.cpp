@@ -429,7 +429,14 @@ extern "C" int fhe_debug_valu_rate(int device, int op, double* lane_ops_per_s) {
 }
 
 extern "C" int fhe_debug_cmux(int device, int arith, const uint32_t* bk_i, int32_t abar, uint32_t* acc) {
-    if (!bk_i || !acc || abar < 0 || abar >= 2 * (int)kN || (arith != 0 && arith != 1))
+    if (arith != 0 && arith != 1) return set_error(FHE_EINVAL, "fhe_debug_cmux: bad argument");
+    const fhe_launch_config cfg{arith == 0 ? 1u : 4u, 1u, (uint32_t)arith};
+    return fhe_debug_cmux_shape(device, &cfg, bk_i, abar, acc);
+}
+
+extern "C" int fhe_debug_cmux_shape(int device, const fhe_launch_config* cfg, const uint32_t* bk_i, int32_t abar,
+                                    uint32_t* acc) {
+    if (!cfg || !shape_valid(*cfg) || !bk_i || !acc || abar < 0 || abar >= 2 * (int)kN)
         return set_error(FHE_EINVAL, "fhe_debug_cmux: bad argument");
     int rc = check_gfx950(device);
     if (rc) return rc;
@@ -440,39 +447,53 @@ extern "C" int fhe_debug_cmux(int device, int arith, const uint32_t* bk_i, int32
     make_roots(roots);
     uint64_t *d_twf = nullptr, *d_twi = nullptr, *d_bkd = nullptr;
     uint32_t *d_bk = nullptr, *d_acc = nullptr;
-    dev::fft::cd *d_roots = nullptr, *d_bkn = nullptr;
-    const size_t bk_words = 4 * 2 * kN, bkd_words = 2 * 32 * 2 * 64;
-    const size_t roots_bytes = roots.size() * sizeof(dev::fft::cd), bkn_bytes = dev::kKeyStep * sizeof(dev::fft::cd);
+    dev::fft::cd *d_roots = nullptr, *d_bkc = nullptr, *d_bkn = nullptr;
+    const size_t bk_words = 4 * 2 * kN, bkd_words = 2 * 32 * 2 * 64, acc_bytes = 2 * kN * 4;
+    const size_t roots_bytes = roots.size() * sizeof(dev::fft::cd), key_bytes = dev::kKeyStep * sizeof(dev::fft::cd);
+    // a group steps four gates at once: all four start from acc and must agree
+    const size_t copies = cfg->arith == 1 && cfg->waves_per_gate == 1 ? 4 : 1;
+    std::vector<uint32_t> result(copies * 2 * kN);
     hipError_t e = hipSuccess;
     auto step = [&](hipError_t r) { if (e == hipSuccess) e = r; };
     step(hipMalloc((void**)&d_twf, 8192));
     step(hipMalloc((void**)&d_twi, 8192));
     step(hipMalloc((void**)&d_bkd, bkd_words * 8));
     step(hipMalloc((void**)&d_roots, roots_bytes));
-    step(hipMalloc((void**)&d_bkn, bkn_bytes));
+    step(hipMalloc((void**)&d_bkc, key_bytes));
+    step(hipMalloc((void**)&d_bkn, key_bytes));
     step(hipMalloc((void**)&d_bk, bk_words * 4));
-    step(hipMalloc((void**)&d_acc, 2 * kN * 4));
+    step(hipMalloc((void**)&d_acc, copies * acc_bytes));
     if (e == hipSuccess) {
         step(hipMemcpy(d_twf, twf.data(), 8192, hipMemcpyHostToDevice));
         step(hipMemcpy(d_twi, twi.data(), 8192, hipMemcpyHostToDevice));
         step(hipMemcpy(d_roots, roots.data(), roots_bytes, hipMemcpyHostToDevice));
         step(hipMemcpy(d_bk, bk_i, bk_words * 4, hipMemcpyHostToDevice));
-        step(hipMemcpy(d_acc, acc, 2 * kN * 4, hipMemcpyHostToDevice));
+        for (size_t k = 0; k < copies; ++k)
+            step(hipMemcpy(d_acc + k * 2 * kN, acc, acc_bytes, hipMemcpyHostToDevice));
     }
     if (e == hipSuccess)
-        step(arith == 0 ? dev::launch_bk_prepare(d_bk, d_bkd, d_twf, 1, nullptr)
-                        : dev::launch_bk_prepare_fft(d_bk, nullptr, d_bkn, d_roots, 1, nullptr));
+        step(cfg->arith == 0 ? dev::launch_bk_prepare(d_bk, d_bkd, d_twf, 1, nullptr)
+                             : dev::launch_bk_prepare_fft(d_bk, d_bkc, d_bkn, d_roots, 1, nullptr));
     dev::DeviceKeys K{};
+    K.bkd = d_bkd;
     K.twf = d_twf;
     K.twi = d_twi;
+    K.bkc = d_bkc;
     K.bkn = d_bkn;
     K.roots = d_roots;
-    if (e == hipSuccess) step(dev::launch_debug_cmux(K, arith, d_bkd, abar, d_acc, nullptr));
+    const dev::LaunchConfig shape{cfg->waves_per_gate, cfg->gates_per_group, cfg->arith};
+    if (e == hipSuccess) step(dev::launch_debug_cmux(K, shape, abar, d_acc, nullptr));
     if (e == hipSuccess) step(hipDeviceSynchronize());
-    if (e == hipSuccess) step(hipMemcpy(acc, d_acc, 2 * kN * 4, hipMemcpyDeviceToHost));
-    for (void* p : {(void*)d_twf, (void*)d_twi, (void*)d_bkd, (void*)d_roots, (void*)d_bkn, (void*)d_bk, (void*)d_acc})
+    if (e == hipSuccess) step(hipMemcpy(result.data(), d_acc, copies * acc_bytes, hipMemcpyDeviceToHost));
+    for (void* p : {(void*)d_twf, (void*)d_twi, (void*)d_bkd, (void*)d_roots, (void*)d_bkc, (void*)d_bkn,
+                    (void*)d_bk, (void*)d_acc})
         if (p) (void)hipFree(p);
-    return e == hipSuccess ? FHE_OK : hip_fail(e, "fhe_debug_cmux");
+    if (e != hipSuccess) return hip_fail(e, "fhe_debug_cmux");
+    for (size_t k = 1; k < copies; ++k)
+        if (std::memcmp(result.data(), result.data() + k * 2 * kN, acc_bytes) != 0)
+            return set_error(FHE_EDEVICE, "fhe_debug_cmux: gate %zu of the group differs from gate 0", k);
+    std::memcpy(acc, result.data(), acc_bytes);
+    return FHE_OK;
 }
 
 extern "C" int fhe_ctx_set_timing(fhe_ctx* ctx, int enable) {

@@ -82,6 +82,7 @@ void make_roots(std::vector<dev::fft::cd>& roots);
 int ctx_reserve_big(fhe_ctx* ctx, size_t gates);
 // Launch-shape table (tuner.cpp).
 int tune_bucket(size_t width);
+bool shape_valid(const fhe_launch_config& c);
 void tune_defaults(fhe_ctx* ctx);
 dev::LaunchConfig launch_config_for(const fhe_ctx* ctx, size_t width);
 // Enqueues blind rotation + key switching of `count` gates on stream s

@@ -28,6 +28,8 @@ bool same(const dev::LaunchConfig& a, const dev::LaunchConfig& b) {
     return a.waves_per_gate == b.waves_per_gate && a.gates_per_group == b.gates_per_group && a.arith == b.arith;
 }
 
+}  // namespace
+
 bool shape_valid(const fhe_launch_config& c) {
     if (c.arith > 1) return false;
     if (c.waves_per_gate == 1)
@@ -35,8 +37,6 @@ bool shape_valid(const fhe_launch_config& c) {
     if (c.waves_per_gate == 4) return c.gates_per_group == 1 && c.arith == 1;
     return c.waves_per_gate == 2 && c.gates_per_group == 1;
 }
-
-}  // namespace
 
 int tune_bucket(size_t width) {
     int b = 0;
