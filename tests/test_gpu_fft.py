@@ -74,3 +74,21 @@ def test_group_kernel_inputs_and_outputs(env):
     assert not F.to_host(out)[[1, 5]].any() and F.to_host(out)[[0, 2, 3, 4]].any(axis=1).all()
     with pytest.raises(F.FheError):
         F.fhe_ctx_check(ctx)
+
+
+@pytest.mark.parametrize("shape", [(1, 4, 1), (2, 1, 1), (4, 1, 1)])
+def test_valid_gates_beside_invalid_codes(env, shape):
+    """Gates that share a group (or a launch) with invalid codes have the
+    oracle's words."""
+    import torch
+    ctx, K, _, c, _ = env
+    n, valid = 6, [0, 2, 3, 4]
+    ops = np.array([F.AND, 200, F.XOR, F.OR, F.NAND, F.MAJ], np.uint8)
+    a, b = F.to_device(c[0][:n]), F.to_device(c[1][:n])
+    out = torch.full_like(a, 7)
+    with_shape(ctx, shape, lambda: F.fhe_bootstrap_gate_batch(ctx, torch.from_numpy(ops).cuda(), a, b, out, n))
+    got = F.to_host(out)
+    np.testing.assert_array_equal(got[valid], K.bootstrap(ops[valid], c[0][valid], c[1][valid], threads=8))
+    assert not got[[1, 5]].any()
+    with pytest.raises(F.FheError):
+        F.fhe_ctx_check(ctx)
