@@ -10,18 +10,36 @@
 // signed halves, |k_hi|, |k_lo| <= 2^15, and each half gets its own product
 // V_hi, V_lo with the digits, |digit| <= 2^9.  Every coefficient of the sum
 // over four rows is an integer below 4 * 1024 * 2^9 * 2^15 = 2^36, and
-// rounding the computed real number to the nearest integer recovers it: with
-// u = 2^-53, a butterfly of two fused multiply-adds per component (see
-// butterfly()) adds an error of at most 5.8 u of its outputs' Euclidean norm
-// (twiddles are correctly rounded; the digits' first level, on sums of
-// integers, less), so nine levels add 52 u, in the digits' transform, in the
-// key's and in the inverse alike; the multiply-add over four rows and the final
-// twist add less than 16 u.  The Euclidean norms are at most 2^9 * 2^5 (digits)
-// and 2^15 * 2^5 (key half) per row, and a coefficient of a product is at most
-// the product of the norms: the error is below
-// 4 * 2^14 * 2^20 * 172 u = 172 * 2^-17 < 0.0014, where 0.5 would be
-// needed to round wrongly.  The result V_lo + 2^16 V_hi mod 2^32 is therefore
-// the definition's, bit for bit.
+// rounding the computed real number to the nearest integer recovers it.  With
+// u = 2^-53, to first order in u, z and k the polynomials of a row's digits and
+// of a key half (|z| <= 2^14, |k| <= 2^20 in the Euclidean norm), X and K their
+// exact values at the 512 roots (|X| = 512^(1/2) |z|, likewise K) and B the sum
+// of |z| |k| over the rows, at most 2^36:
+//  - A butterfly r = a + w b, s = 2 a - r (see butterfly()) computes r to
+//    u (|a| + 2 |b| + |r|): two roundings per component and one of w.  s adds
+//    u |s|.  Both errors together are at most 5.46 u of the norm of (a, b), that is
+//    3.9 u of the norm of (r, s); the digits' first level, on sums of integers,
+//    and twiddles of 1 and -i less.
+//  - Forward, nine levels: the computed spectra are within 36 u |X| and 36 u |K|
+//    of the exact ones (roots and constants are correctly rounded).  By Cauchy
+//    and Schwarz the products of a row are then within 72 u |X| |K| = 512 * 72 u
+//    |z| |k|, summed over the roots.
+//  - Multiply-add: at most 16 roundings per component, each of a partial sum below
+//    the sum of the |X_p| |K_p| over the rows: 512 * 24 u B summed over the roots.
+//  - Every coefficient is the sum of 512 products S_p with weights of magnitude
+//    1/512 (exact, in the key), so that it inherits at most 96 u B of these.
+//  - Inverse: every intermediate value is a sum of its own leaves with such
+//    weights, so those of one level are together at most the sum of the
+//    |S_p| / 512, which is at most B; a butterfly's outputs are within
+//    4 u (|a| + |b|); and each coefficient gets each level's errors once from
+//    every node, with weights of magnitude one: 4 u B per level.  A product with
+//    a rounded factor (the factors between the group kernel's two transforms, a
+//    twist) adds 3 u B.  Group kernel: nine levels and two products, 42 u B.
+//    Narrow kernel: eight levels, one product and the join of the halves (4 u B),
+//    39 u B.
+// Altogether at most 138 u B <= 138 * 2^-17 < 0.0011, where 0.5 would be needed
+// to round wrongly, for any key and any digits.  The result V_lo + 2^16 V_hi mod
+// 2^32 is therefore the definition's, bit for bit.
 //
 // Transforms.  Forward: Cooley-Tukey on the ring, X^(2m) - w^2 splitting into
 // (X^m - w)(X^m + w), i.e. (a, b) -> (a + w b, a - w b); a node is named by
