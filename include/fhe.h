@@ -356,9 +356,11 @@ int fhe_ctx_set_graphs(fhe_ctx* ctx, int enable);
 /* every width above 2^14).  Shapes:                                        */
 /*   waves_per_gate = 1, gates_per_group in {1, 2, 4, 8}: one wavefront per */
 /*     gate (throughput shape); arith 0: that many ciphertexts per          */
-/*     workgroup; arith 1: always groups of four ciphertexts that share     */
-/*     their key loads;                                                     */
-/*   waves_per_gate = 2, gates_per_group = 1: latency shape for levels       */
+/*     workgroup; arith 1: groups of four ciphertexts that share their key  */
+/*     loads, whatever gates_per_group (four names of one shape), and where */
+/*     the last round of groups would leave most of the chip idle, its      */
+/*     gates (at most two per compute unit) run on the latency kernels;     */
+/*   waves_per_gate = 2, gates_per_group = 1: latency shape for levels      */
 /*     narrower than the chip (arith 0: two wavefronts split every CMux of  */
 /*     one gate; arith 1: eight, two gates per compute unit);               */
 /*   each of these with either arithmetic (arith 0 or 1);                   */
@@ -376,8 +378,8 @@ typedef struct {
                         the rounding of every product exact (both exact) */
 } fhe_launch_config;
 
-/* Times every shape on synthetic gate batches of width 1, 2, 4, ... up to
- * max_width (at most 2^15; reps timed runs each after one warm-up run, the
+/* Times every shape (of equal ones {1, 4, 1}) on synthetic gate batches of
+ * width 1, 2, 4, ... up to max_width (at most 2^15; reps timed runs each after one warm-up run, the
  * fastest kept) on the context's device and stores the fastest shape per
  * bucket (the default shape of a bucket stays unless another is more than
  * 2% faster); wider buckets take the widest measured one's.  Synchronous:
@@ -500,8 +502,9 @@ int fhe_ctx_set_timing(fhe_ctx* ctx, int enable);
 int fhe_ctx_timing(fhe_ctx* ctx, double* blind_rotate_ms, double* key_switch_ms,
                    uint64_t* launches, uint64_t* gates);
 
-/* The same records launch by launch, with the shape each ran with.  Waits
- * for the recorded work; writes min(recorded, max) records in launch order
+/* The same records launch by launch, with the shape each ran with (a batch in
+ * groups whose last gates ran on a latency kernel is one record, with the
+ * groups' shape and the time of both).  Waits for the recorded work; writes min(recorded, max) records in launch order
  * to out, the number recorded to *count, and resets the records. */
 typedef struct {
     uint64_t gates;

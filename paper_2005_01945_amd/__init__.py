@@ -399,9 +399,10 @@ def fhe_ctx_set_graphs(ctx, enable):
     _check(lib().fhe_ctx_set_graphs(ctx.h, 1 if enable else 0), "fhe_ctx_set_graphs")
 
 
-# Launch shapes of the blind-rotation kernel (the autotuner's search space):
-# (waves_per_gate, gates_per_group, arith), arith 0 = Goldilocks NTT,
-# 1 = double-precision FFT.
+# Launch shapes of blind rotation: (waves_per_gate, gates_per_group, arith),
+# arith 0 = Goldilocks NTT, 1 = double-precision FFT.  (1, 1, 1), (1, 2, 1),
+# (1, 4, 1) and (1, 8, 1) are names of one shape, groups of four gates; the
+# autotuner times it once.
 SHAPES = [(w, g, a) for a in (0, 1) for (w, g) in ((1, 1), (1, 2), (1, 4), (1, 8), (2, 1))] + [(4, 1, 1)]
 
 
@@ -424,7 +425,7 @@ def fhe_ctx_set_launch_config(ctx, min_width, max_width, shape):
 
 def fhe_ctx_timing_launches(ctx, max_records=1 << 16):
     """Per-launch records since the last timing call: list of dicts with
-    gates, shape (waves_per_gate, gates_per_group), blind_rotate_ms,
+    gates, shape (waves_per_gate, gates_per_group, arith), blind_rotate_ms,
     key_switch_ms."""
     buf = (fhe_launch_record * max_records)()
     n = C.c_size_t()

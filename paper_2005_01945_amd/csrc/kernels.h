@@ -78,8 +78,10 @@ hipError_t launch_bk_prepare_fft(const uint32_t* bk, fft::cd* bkc, fft::cd* bkn,
 //     {1, 2, 4, 8} gates share a workgroup (and its twiddle copy in LDS);
 //     waves_per_gate = 2: two waves split each CMux of one gate.
 //   arith 1: waves_per_gate = 1: groups of four gates on four waves, whatever
-//     gates_per_group; waves_per_gate = 2 and 4: eight waves per gate, two per
-//     digit row, laid out for two gates per compute unit (2) or one (4).
+//     gates_per_group, and the other kernels for the gates of a short last round
+//     (narrow_tail in kernels.hip); waves_per_gate = 2 and 4: eight waves per
+//     gate, two per digit row, laid out for two gates per compute unit (2) or
+//     one (4).
 // Every shape gives the same words.
 struct LaunchConfig {
     uint32_t waves_per_gate;

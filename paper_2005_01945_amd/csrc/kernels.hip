@@ -1098,13 +1098,14 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 }
 
 // Blind rotation with FFT products on eight wavefronts per gate, for batches
-// that leave compute units with one gate (LEAN = false: one gate 1.40 ms, 256
-// gates 1.71 ms) or two (LEAN: 512 gates 2.86 ms, 300 gates 2.60).  A step of
+// that leave compute units with one gate (LEAN = false: one gate 1.42 ms, 256
+// gates 1.47 ms) or two (LEAN: 512 gates 2.72 ms, 300 gates 2.56).  A step of
 // one gate takes 6,700 cycles, a chain of LDS round trips and four barriers
 // around 495 VALU per wave; two waves per SIMD fill each other's gaps.  With
 // two gates LDS is busy 70% of the time, most of it writes (64 B per clock).
-// Both exchanges of lane bits 3 to 0 through LDS: 1.53 and 3.08 ms (bits 1 and
-// 0 by moves as well, which need selects: 1.46 and 2.96).  The 128 KB of key
+// Both exchanges of lane bits 3 to 0 through LDS: one gate 1.53 ms and 512 gates
+// 3.08, where this form took 1.40 and 2.86 (bits 1 and 0 by moves as well, which
+// need selects: 1.46 and 2.96).  The 128 KB of key
 // per step and gate are 2,000 cycles of the vector memory path, so the loads
 // are spread over the step: all in one place they cost 0.3 ms.  Four wavefronts
 // per gate, one per row: 2.06 and 4.2 ms; two: 2.54 and 3.3.  The integer NTTs
@@ -1183,7 +1184,7 @@ void k_blind_rotate_narrow(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, 
 // 128 matrix instructions of 16 cycles per wave and step, 12,500 of the 15,000
 // cycles that a step takes per wave at two waves per SIMD; LDS is busy a third
 // of the time, its writes (64 B per clock) most of it.  16,384 gates in 51 ms,
-// 2,048 in 7.2 ms, 1,024 (one wave per SIMD) in 4.5 ms.  With a masked address
+// 2,048 in 7.0 ms, 1,024 (one wave per SIMD) in 4.5 ms.  With a masked address
 // and a sign of its own for each rotated word, and the first level in doubles:
 // 2,310 VALU, 52.0 ms (with the reads spread among the arithmetic 53.7).  The
 // integer NTTs modulo two 28-bit primes that this replaces issued 6,570 VALU per
@@ -1345,7 +1346,9 @@ void k_blind_rotate_group(DeviceKeys K, GateIO io, uint32_t* __restrict__ big, u
         // loads: the first twelve wait in the wave's own rows, idle until the
         // inverse exchange, while the transform runs (12 staged and a window
         // of 8: 13.65 ms at 4,096 gates; a window of 4 and none staged, 14.0;
-        // all staged, 14.1; a window of 8 and none staged spills, 14.8).
+        // all staged, 14.1; a window of 8 and none staged spills more, 14.8).
+        // This form keeps nine registers in scratch; a step stores one word of
+        // them and reads three.
 #pragma unroll
         for (int k = 0; k < kStaged; ++k) load_key_lds(keyw + k * 256, lane16, kslot + 1024 * k);
         fft::forward_lane<32>(y, [&](auto k) { return tf[16 * decltype(k)::value]; });
@@ -1717,20 +1720,17 @@ hipError_t launch_bk_prepare(const uint32_t* bk, uint64_t* bkd, const uint64_t* 
     return hipGetLastError();
 }
 
-// Arithmetic 1 with one wave per gate always runs groups of four gates: the
-// share of the key loads that a smaller group would lose costs more than its
-// idle waves (one gate: 4.8 ms in a group, 18.7 ms on a wave by itself).
 // How many gates at the end of a wide batch of `count` run on the narrow kernel
 // after the groups.  Groups fill the chip in rounds of eight gates per compute
 // unit; a last round of up to four per unit still takes 4.4 ms and one of more
 // 7.0 ms, and leaves most of the chip idle when it is short.  The narrow kernel
-// does one gate per unit in 1.7 ms and two in 2.9 (256 units; blind rotation, ms,
+// does one gate per unit in 1.5 ms and two in 2.7 (256 units; blind rotation, ms,
 // all groups / with a tail):
-//   rest up to 2 per unit:     2,049 gates 11.3 / 8.9, 2,560 gates 11.0 / 9.8,
-//                              16,385 gates 56.2 / 54.1
-//   rest over 4, to 5 per unit: 1,025 to 1,280 gates 7.1 / 6.0
-// Between 2 and 4 per unit the narrow kernel needs 4.4 ms or more itself, and
-// past 5 per unit the two parts (4.5 + 2.9) are slower than one round.
+//   rest up to 2 per unit:     2,049 gates 11.3 / 8.9, 2,560 gates 11.0 / 9.7,
+//                              16,385 gates 56.2 / 53.5
+//   rest over 4, to 5 per unit: 1,025 to 1,280 gates 7.1 / 5.9
+// With three per unit the narrow kernel takes 4.26 ms itself and with four 5.35,
+// and past 5 per unit the two parts (4.4 + 2.7) take as long as one round.
 static uint32_t narrow_tail(uint32_t count, uint32_t cus) {
     const uint32_t rest = count % (8 * cus);
     if (count > rest && rest <= 2 * cus) return rest;
@@ -1756,6 +1756,8 @@ hipError_t launch_blind_rotate(const DeviceKeys& K, const GateIO& io, uint32_t* 
     };
     if (cfg.arith == 1) {
         switch (cfg.waves_per_gate) {
+        // groups of four gates, whatever cfg.gates_per_group (a wave per gate, which
+        // shares no key loads, was dropped: 18.7 ms for one gate, a group 4.4)
         case 1: {
             const uint32_t tail = narrow_tail(count, cus);
             if (tail) {
@@ -1806,7 +1808,7 @@ hipError_t launch_key_switch(const DeviceKeys& K, const GateIO& io, const uint32
     //   <2, 2, 16>  30 / 30 / 34 /  65 /   918
     //   <2, 4,  8>  49 / 47 / 48 /  56 /   808   (0.41 of the int8 rate)
     // Four waves on four gate groups that share B through L1 instead of the
-    // split over steps: 998 at 16,384.
+    // split over steps: 998 at 16,384.  (<2, 2, 16> keeps one register in scratch.)
     if (count <= 128) return launch_key_switch_shape<1, 1, 16>(K, io, big, count, s);
     if (count <= 256) return launch_key_switch_shape<2, 1, 16>(K, io, big, count, s);
     if (count <= 512) return launch_key_switch_shape<2, 2, 16>(K, io, big, count, s);

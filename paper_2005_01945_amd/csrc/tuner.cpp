@@ -46,9 +46,9 @@ int tune_bucket(size_t width) {
 
 // Before any measurement: FFT arithmetic everywhere; the one-gate-per-CU layout
 // up to one gate per CU, the two-gate one up to two, groups of four gates
-// beyond.  Measured blind rotations (ms) at 256 / 512 / 1,024 gates on 256 CUs:
-// one gate per CU 1.71 / 3.04 / 5.72, two 1.81 / 2.86 / 5.41, groups 4.5 / 4.5 /
-// 4.5.
+// beyond.  Measured blind rotations (ms) at 256 / 512 / 768 / 1,024 gates on 256
+// CUs: one gate per CU 1.47 / 2.91 / - / 5.8, two 1.65 / 2.72 / 4.26 / 5.35,
+// groups 4.43 / 4.44 / 4.46 / 4.48.
 static dev::LaunchConfig default_shape(const fhe_ctx* ctx, size_t width) {
     const size_t cus = (size_t)ctx->cu_count;
     if (width <= cus) return dev::LaunchConfig{4, 1, 1};

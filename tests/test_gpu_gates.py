@@ -1,7 +1,7 @@
 """GPU parity of gate bootstrapping: the HIP path through the C ABI against the
-CPU oracle, ciphertext word for ciphertext word (bit-exact: both NTT
-arithmetics, two 28-bit primes with CRT and 2^64 - 2^32 + 1, give the exact
-negacyclic products, so no tolerance applies)."""
+CPU oracle, ciphertext word for ciphertext word (bit-exact: both arithmetics,
+double-precision FFTs with the key in 16-bit halves and NTTs modulo
+2^64 - 2^32 + 1, give the exact negacyclic products, so no tolerance applies)."""
 import numpy as np
 import pytest
 

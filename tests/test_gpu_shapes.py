@@ -1,7 +1,8 @@
-"""Launch shapes and the autotuner: every blind-rotation shape (one wave per
-gate with 1, 2, 4 or 8 gates per workgroup, or two or four waves per gate;
-NTT over the Goldilocks prime or modulo two 28-bit primes) gives the
-oracle's words bit for bit, and the tuner only ever stores such shapes."""
+"""Launch shapes and the autotuner: every blind-rotation shape (NTT over the
+Goldilocks prime with one wave per gate and 1, 2, 4 or 8 gates per workgroup or
+two waves per gate; double-precision FFT in groups of four gates, under its four
+names, or with one or two gates per compute unit) gives the oracle's words bit
+for bit, and the tuner only ever stores such shapes."""
 import numpy as np
 import pytest
 
