@@ -377,7 +377,7 @@ std::vector<uint32_t> asap_levels(const Circuit& c, uint32_t* depth) {
 // from the measured shape timings: what is left over after the whole rounds
 // runs on the narrower shapes or as a part of a round.  Up to an eighth of a
 // round takes 1.47 ms, a quarter 2.72, a half 4.48, five eighths 5.98, that is
-// 0.21, 0.39, 0.64 and 0.86 of a round with key switching.  The first two are
+// 0.21, 0.39, 0.64 and 0.85 of a round with key switching.  The first two are
 // charged a little more, as they were first measured (1.72 and 2.87 ms); with
 // 0.21 and 0.385 two of 195 schedules of built-in circuits differ.
 static double level_cost(uint64_t gates, uint64_t round) {
